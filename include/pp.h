@@ -318,7 +318,7 @@ int32_t pp_run_group_words(pp_run r);
 /* Per-round record of the last pp_propagate_* call: for each round r <= the
  * current round, mode[r] (PP_MODE_PULL, PP_MODE_PUSH, PP_MODE_PUSH_FLAT or
  * PP_MODE_SPARSE_PULL; 2 for round 0, the initialisation) and arcs[r] (arcs the round touched: all
- * arcs for a pull, the changed nodes' predecessor arcs for a sparse round).
+ * arcs for a pull, also where it may stop lists early; the changed nodes' predecessor arcs for a sparse round).
  * Host arrays of cap entries; either may be NULL. */
 int pp_get_round_log(pp_run r, int32_t *mode, int64_t *arcs, int32_t cap);
 /* The same record for one seed group of a run (pp_get_round_log: group 0's

@@ -109,6 +109,10 @@ struct Ctrl {
     int32_t flat;         // bit 0: the sparse round about to run walks its frontier as flattened
                           // arc ranges (read before atomics) rather than direct slots per entry;
                           // bit 1: the fixed threshold's choice (frontier >= PUSH_FILTER_MIN)
+    uint64_t gain[8];     // seed bits that any node gained in the pull round being run
+    uint64_t live[8];     // seed bits that any node gained in round exit_round - 1
+    int32_t exit_round;   // this round, if it pulls, stops each node's list early (0: none)
+    int32_t pad_exit;
 };
 
 static_assert(sizeof(Ctrl) % 4 == 0, "the control block is staged to the host as 32-bit words");
@@ -178,7 +182,36 @@ struct GraphDev {
                                  // successors: the pull launches its short-list form
     int32_t skip_dead;           // the pull leaves the rows of nodes without successors
                                  // alone (many such nodes, rows beyond the caches)
+    int32_t exit_ok;             // late pulls may stop lists early (one graph, not the short-list form)
+    int64_t open_nodes;          // nodes with successors
 };
+
+// The early-exit pull (phase_pull_exit).
+// Successors of a node gathered per step: with the hub-first order the first
+// few rows settle most nodes (R-MAT 20, round 4: 2 per step would gather 0.08
+// of the arcs, 4 0.11, 8 0.15, 16 0.25, but each step costs two dependent loads).
+constexpr int EXIT_STEP = 4;
+// arcs after which a node still short of a live bit leaves the rest of its
+// list to chunks of EXIT_CHUNK arcs, one wave each (R-MAT 24, four words:
+// round 4 takes 802 us at 16, 644 at 32, 600 at 64, 723 at 128 with the first
+// form's 32768 blocks)
+constexpr int EXIT_LIMIT = 64;
+constexpr int EXIT_CHUNK = 256;
+// a pull takes the form from one part in EXIT_SHARE of the (node with
+// successors, live seed) pairs reached on: below, few rows can hold every live
+// bit (R-MAT 18, round 3: 0.04 reached, 0.85 of the arcs would be gathered all
+// the same; round 4: 0.6 reached, 0.11 gathered)
+constexpr int EXIT_SHARE = 8;
+// and on graphs with this many arcs or more: below, a round is bound by its
+// launches and the steps' dependent loads add to it (undirected R-MAT 13,
+// 512 seeds: 3.9 -> 4.5 ms for its 16 groups; ER 10k: 192 -> 204 us; but
+// undirected R-MAT 17, 4M arcs: round 4 96 -> 45 us)
+constexpr int64_t EXIT_MIN_ARCS = (int64_t)1 << 20;
+// blocks of the launch that take part (half of them with eight-word rows):
+// as many as are resident at once, since each block's start and sums cost more
+// than its share of a late round (R-MAT 24, eight words, the third pull: 1175
+// us with 32768 blocks, 952 with 1024)
+constexpr int EXIT_BLOCKS = 1024;
 
 // A pull tile whose nodes have at most PULL_NPL successors each gathers with
 // one lane per node (rows of one or two words).

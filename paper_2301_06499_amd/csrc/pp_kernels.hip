@@ -15,7 +15,10 @@
 //                    the other signature buffer (the update is synchronous
 //                    because Sig_{r-1} is only read).  New bits are counted
 //                    per block (Algorithm 1's XOR count).  Chunks of
-//                    high-degree nodes OR into the accumulator.
+//                    high-degree nodes OR into the accumulator.  Late pulls of
+//                    large graphs stop each node's list once it holds every
+//                    bit that anyone gained in the last round
+//                    (phase_pull_exit).
 // Sparse push (equal to the pull: only the bits a node gained in round r-1
 // can give new bits in round r, every older bit having reached its
 // predecessors already):
@@ -762,6 +765,24 @@ PP_DEV void phase_push_commit(const GraphDev &g, const RunDev &R, int init, int 
 
 // ---------------------------------------------------------------- pull
 
+// The seed bits a pull round found new, into the control block's gain: gm is
+// the thread's OR of new bits of word threadIdx.x % W.  Bits only get set, so
+// a block whose bits are all there already (nearly every block but the first
+// few) reads the words and adds nothing.  Every thread of the block calls.
+template <int W> PP_DEV void add_gain(Ctrl *C, uint64_t gm) {
+    __shared__ unsigned long long s_gain[BLOCK / 64][W];
+#pragma unroll
+    for (int o = 32; o >= W; o >>= 1) gm |= __shfl_xor(gm, o);
+    if (lane_id() < W) s_gain[threadIdx.x >> 6][lane_id()] = gm;
+    __syncthreads();
+    if (threadIdx.x < W) {
+        unsigned long long v = 0;
+#pragma unroll
+        for (int k = 0; k < BLOCK / 64; ++k) v |= s_gain[k][threadIdx.x];
+        if (v & ~CTL(C->gain[threadIdx.x])) atomicOr((unsigned long long *)&C->gain[threadIdx.x], v);
+    }
+}
+
 // Issues the loads that stage a pull tile: K column ids per lane and the
 // tile's row offsets (relative to its first arc; a hub chunk is one row).
 template <int K, int NODES>
@@ -781,6 +802,14 @@ PP_DEV void stage_tile(const GraphDev &g, const Tile &T, int ln, int32_t (&cv)[K
         if (ln <= nn) rv0 = (int)(g.rp[T.u0 + ln] - T.e0);
         if (ln == 0 && nn == NODES) rv1 = (int)(g.rp[T.u0 + NODES] - T.e0);
     }
+}
+
+// Whether node ln of the wave's nodes has a bit in m, the ballot over words
+// 64 j .. 64 j + 63 of their rows (W words per node); false when node ln's
+// words lie in another ballot.
+template <int W> PP_DEV bool node_bit(uint64_t m, int j) {
+    const int at = lane_id() * W;
+    return (at >> 6) == j && ((m >> (at & 63)) & WordMask<W>::row) != 0;
 }
 
 // SHORT: every tile of the graph takes the one-lane-per-node gather (rows of
@@ -811,6 +840,7 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
     unsigned long long *acc_l = s_acc[wv];
     const bool per_seed = R.seed_counts != nullptr;
     uint64_t pop = 0;
+    uint64_t gm = 0;   // new bits of the lane's word of a row (word ln % W)
     int64_t nodes = 0, parcs = 0, pulled = 0;
     uint32_t sc[W];
 #pragma unroll
@@ -958,30 +988,32 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
             if (ln < W && acc_l[ln]) atomicOr((unsigned long long *)&R.acc[(int64_t)T.u0 * W + ln], acc_l[ln]);
         } else {
             uint64_t tpop = 0;
+            bool changed = false;   // the tile's node ln
 #pragma unroll
             for (int j = 0; j < W; ++j) {   // same trip count for every lane
                 const int idx = ln + j * 64;
                 const bool valid = idx < nn * W;
                 uint64_t nw2 = 0;
-                const int32_t u = T.u0 + idx / W;
                 if (DEAD ? ((rowmask >> (idx / W)) & 1ull) != 0 : valid) {
                     const uint64_t av = acc_l[idx];
                     nw2 = av & ~own[j];
                     nxt[(int64_t)T.u0 * W + idx] = own[j] | av;
                 }
                 tpop += (uint64_t)__popcll(nw2);
-                const uint64_t bal = __ballot(nw2 != 0);
-                const int gb = ln & ~(W - 1);
-                const bool lead = valid && (ln & (W - 1)) == 0 && ((bal >> gb) & WordMask<W>::row) != 0;
-                if (lead) {
-                    nodes += 1;
-                    parcs += g.trp[u + 1] - g.trp[u];
-                    R.stamp[u] = r;   // changed in this round: listed by a push that follows
-                }
+                gm |= nw2;
+                changed |= node_bit<W>(__ballot(nw2 != 0), j);
                 if (per_seed) {
                     if (R.G == 1) seed_ballot<W>(nw2, sc);
                     else seed_bits_keyed<W>(R, r, T.graph, nw2, valid);
                 }
+            }
+            // one lane per changed node, after all of the tile's words: one
+            // coalesced wait for the degrees instead of one per word
+            if (changed) {
+                const int32_t u = T.u0 + ln;
+                nodes += 1;
+                parcs += g.trp[u + 1] - g.trp[u];
+                R.stamp[u] = r;   // changed in this round: listed by a push that follows
             }
             if (R.G == 1) {
                 pop += tpop;
@@ -1002,15 +1034,304 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
         R.blk_arcs[bid] = (int64_t)ta;
         R.blk_pulled[bid] = (int64_t)tq;
     }
+    if (g.exit_ok) add_gain<W>(C, gm);
     if (per_seed && R.G == 1) seed_flush<W>(R, r, sc);
 }
 
-// High-degree nodes of a pull round: the chunks left their ORed rows in the
-// accumulator.
+// A wave's LDS writes before, its LDS reads after (no instruction moves across).
+PP_DEV void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The pull of a late round, stopping each list early.  A node gains in round r
+// only bits that some node gained in round r-1 (live: the OR of that round's
+// new bits), so a node whose row holds every live bit gathers nothing, and a
+// node that gathers may stop at the first successor after which it holds them
+// all: the bits it has then are the bits its whole list would give.  Lists are
+// sorted by stored id and the most-gathered rows are stored first, so a list's
+// first successors are the likeliest to hold everything.
+//
+// A wave takes 64 consecutive nodes: their rows (LDS), then the nodes still
+// short of a live bit, handed out to groups of L lanes (16 bytes of a row per
+// lane) which gather EXIT_STEP successors per step; a group that is done takes
+// the next node.  What bounds it is the chain of dependent loads per step
+// (column, then row), not bytes, hence groups of lanes on as many nodes as the
+// wave holds instead of tiles of arcs.  A node short of a live bit after
+// EXIT_LIMIT arcs is listed (list r & 1, not in use in a pull round) and the
+// rest of its list goes to chunks: phase_pull_rest gathers them in the push's
+// launch slot into the accumulator, and the closing launch combines them as it
+// does a dense pull's high-degree nodes.
+// Measured, per round of the third and fourth pulls: R-MAT 20, s = 256, 128 and
+// 126 -> 42 and 36 us; R-MAT 24, s = 512, 4.13 and 4.07 -> 0.99 and 0.71 ms as
+// one group of eight-word rows, 2.92 and 2.92 -> 0.54 and 0.39 ms with seed
+// groups (four words).
 template <int W>
-PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb, int64_t *parts = nullptr) {
+PP_DEV void phase_pull_exit(const GraphDev &g, const RunDev &R, int bid, int nb) {
     Ctrl *C = R.ctrl;
-    if (g.nhubs == 0) {
+    using PS = PullShape<W>;
+    constexpr int L = PS::L, P = PS::P;
+    constexpr int WAVES = BLOCK / 64;
+    constexpr int ST = EXIT_STEP;
+    __shared__ unsigned long long s_row[WAVES][64 * W];
+    __shared__ int64_t s_beg[WAVES][64];
+    __shared__ int32_t s_deg[WAVES][64];
+    __shared__ int32_t s_node[WAVES][64];
+    __shared__ int32_t s_left[WAVES][64];   // arcs left to chunks
+    __shared__ unsigned long long s_red[BLOCK / 64];
+    const int r = CTL(C->round);
+    const int cur = CTL(C->cur);
+    const uint64_t *__restrict__ sig = sel(R.sig, cur);
+    uint64_t *__restrict__ nxt = sel(R.sig, cur ^ 1);
+    const int ln = lane_id(), wv = threadIdx.x >> 6, sub = ln % L;
+    unsigned long long *row_l = s_row[wv];
+    int64_t *beg_l = s_beg[wv];
+    int32_t *deg_l = s_deg[wv], *node_l = s_node[wv], *left_l = s_left[wv];
+    const bool per_seed = R.seed_counts != nullptr;
+    const uint64_t lvw = CTL(C->live[ln & (W - 1)]);   // the lane's word in row order
+    uint64_t lvp[P];                                    // the lane's slice in the gather
+#pragma unroll
+    for (int k = 0; k < P; ++k) lvp[k] = CTL(C->live[sub * P + k]);
+    uint64_t pop = 0, gm = 0;
+    int64_t nodes = 0, parcs = 0, pulled = 0;
+    uint32_t sc[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) sc[k] = 0;
+
+    const int64_t ngrp = (g.n - g.n0 + 63) >> 6;
+    const int64_t nw = (int64_t)nb * WAVES;
+    int64_t t = (int64_t)bid * WAVES + wv;
+    auto offsets = [&](int64_t q, int64_t &b, int64_t &e) {   // the lane's node of group q
+        const int64_t u = g.n0 + q * 64 + ln;
+        const bool in = q < ngrp && u < g.n;
+        b = in ? g.rp[u] : 0;
+        e = in ? g.rp[u + 1] : 0;
+    };
+    int64_t b = 0, e = 0;
+    offsets(t, b, e);
+    for (; t < ngrp; t += nw) {   // wave-uniform
+        const int64_t u0 = g.n0 + t * 64;
+        const int64_t nb0 = b, ne0 = e;
+        const int32_t deg = (int32_t)(ne0 - nb0);
+        const uint64_t rowmask = __ballot(deg > 0);   // a node without successors keeps its row, equal in both buffers
+        uint64_t own[W];
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            const int idx = ln + j * 64;   // word idx % W of node idx / W
+            own[j] = ((rowmask >> (idx / W)) & 1ull) ? sig[u0 * W + idx] : 0ull;
+        }
+        offsets(t + nw, b, e);   // the next group's, in flight during this one
+        if (rowmask == 0) continue;
+        bool need = false;   // the lane's node: short of a live bit?
+#pragma unroll
+        for (int j = 0; j < W; ++j) {
+            row_l[ln + j * 64] = own[j];
+            need |= node_bit<W>(__ballot((lvw & ~own[j]) != 0), j);
+        }
+        need = need && deg > 0;
+        const uint64_t needm = __ballot(need);
+        const int cnt = (int)__popcll(needm);
+        if (need) {
+            const int pos = (int)__popcll(needm & ((1ull << ln) - 1ull));
+            node_l[pos] = ln;
+            beg_l[pos] = nb0;
+            deg_l[pos] = deg;
+        }
+        left_l[ln] = 0;
+        wave_lds_fence();
+        pulled += deg;
+        int mine = -1;   // the group's node (slot of the list), its next arc and arcs left
+        int32_t nd = 0, left = 0, done = 0;
+        int64_t a = 0;
+        uint64_t acc[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) acc[k] = 0;
+        int next = 0;
+        while (true) {   // wave-uniform exit: every group idle and no node left
+            const uint64_t idle = __ballot(mine < 0 && sub == 0);
+            if (mine < 0) {
+                const int q = next + (int)__popcll(idle & ((1ull << (ln - sub)) - 1ull));
+                if (q < cnt) {
+                    mine = q;
+                    nd = node_l[q];
+                    a = beg_l[q];
+                    left = deg_l[q];
+                    done = 0;
+#pragma unroll
+                    for (int k = 0; k < P; ++k) acc[k] = row_l[nd * W + sub * P + k];
+                }
+            }
+            next += (int)__popcll(idle);
+            if (__ballot(mine >= 0) == 0) break;
+            int32_t v[ST];
+#pragma unroll
+            for (int q = 0; q < ST; ++q) v[q] = (mine >= 0 && q < left) ? g.col[a + q] : -1;
+            uint64_t rows[ST][P];
+#pragma unroll
+            for (int q = 0; q < ST; ++q) {
+                if (v[q] >= 0) {
+                    load_row<P>(sig + (int64_t)v[q] * W + sub * P, rows[q]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) rows[q][k] = 0;
+                }
+            }
+            bool lack = false;
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+#pragma unroll
+                for (int q = 0; q < ST; ++q) acc[k] |= rows[q][k];
+                lack |= (lvp[k] & ~acc[k]) != 0;
+            }
+            a += ST;
+            left -= ST;
+            done += ST;
+            const bool more = ((__ballot(mine >= 0 && lack) >> (ln - sub)) & ((1ull << L) - 1ull)) != 0 && left > 0;
+            if (mine >= 0 && (!more || done >= EXIT_LIMIT)) {
+#pragma unroll
+                for (int k = 0; k < P; ++k) row_l[nd * W + sub * P + k] = acc[k];
+                if (more && sub == 0) left_l[nd] = left;
+                mine = -1;
+            }
+        }
+        wave_lds_fence();
+        // nodes left to chunks: listed, their bits so far in the accumulator
+        const int32_t rest = left_l[ln];
+        const uint64_t restm = __ballot(rest > 0);
+        if (restm) {   // wave-uniform
+            const int p = r & 1;
+            const int nch = rest > 0 ? (rest + EXIT_CHUNK - 1) / EXIT_CHUNK : 0;
+            const int incl = wave_inclusive_scan(nch);
+            unsigned long long base = 0;
+            if (ln == 63)
+                base = atomicAdd(reinterpret_cast<unsigned long long *>(&C->lst[p]),
+                                 (unsigned long long)__popcll(restm) | ((unsigned long long)incl << 32));
+            base = __shfl(base, 63);
+            const int ent = (int)(uint32_t)base + (int)__popcll(restm & ((1ull << ln) - 1ull));
+            if (rest > 0) {
+                sel(R.f_ids, p)[ent] = (int32_t)(u0 + ln);
+                Chunk *ch = sel(R.chunks, p) + ((int)(base >> 32) + incl - nch);
+                for (int c = 0; c < nch; ++c) ch[c] = Chunk{ent, deg - rest + c * EXIT_CHUNK};
+            }
+        }
+        bool changed = false;   // the lane's node
+#pragma unroll
+        for (int j = 0; j < W; ++j) {   // same trip count for every lane
+            const int idx = ln + j * 64;
+            const int i = idx / W;
+            const uint64_t av = row_l[idx];
+            uint64_t nw2 = av & ~own[j];
+            if ((restm >> i) & 1ull) {
+                R.acc[u0 * W + idx] = nw2;
+                nw2 = 0;
+            } else if ((rowmask >> i) & 1ull) {
+                nxt[u0 * W + idx] = av;
+            } else {
+                nw2 = 0;
+            }
+            pop += (uint64_t)__popcll(nw2);
+            gm |= nw2;
+            changed |= node_bit<W>(__ballot(nw2 != 0), j);
+            if (per_seed) seed_ballot<W>(nw2, sc);
+        }
+        if (changed) {
+            const int64_t u = u0 + ln;
+            nodes += 1;
+            parcs += g.trp[u + 1] - g.trp[u];
+            R.stamp[u] = r;
+        }
+        wave_lds_fence();
+    }
+    const unsigned long long tp = block_sum<unsigned long long>(pop, s_red);
+    const unsigned long long tn = block_sum<unsigned long long>((unsigned long long)nodes, s_red);
+    const unsigned long long ta = block_sum<unsigned long long>((unsigned long long)parcs, s_red);
+    const unsigned long long tq = block_sum<unsigned long long>((unsigned long long)pulled, s_red);
+    if (threadIdx.x == 0) {
+        R.blk_cnt[bid] = (int64_t)tp;
+        R.blk_nodes[bid] = (int64_t)tn;
+        R.blk_arcs[bid] = (int64_t)ta;
+        R.blk_pulled[bid] = (int64_t)tq;
+    }
+    add_gain<W>(C, gm);
+    if (per_seed) seed_flush<W>(R, r, sc);
+}
+
+// Whether round r, a pull, stops lists early.
+PP_DEV bool exits(const GraphDev &g, const Ctrl *C, int r) { return g.exit_ok && CTL(C->exit_round) == r; }
+
+// Blocks of a pull launch that an early-exit pull uses (the rest leave at once).
+PP_DEV int exit_blocks(int nb, int W) {
+    const int most = W >= 8 ? EXIT_BLOCKS / 2 : EXIT_BLOCKS;
+    return nb < most ? nb : most;
+}
+
+// The chunks an early-exit pull left: one wave ORs up to EXIT_CHUNK arcs of a
+// listed node into its accumulator row, unless the row and the accumulator
+// hold every live bit already (a stale copy only costs the work).
+template <int W>
+PP_DEV void phase_pull_rest(const GraphDev &g, const RunDev &R, int bid, int nb) {
+    Ctrl *C = R.ctrl;
+    using PS = PullShape<W>;
+    constexpr int L = PS::L, P = PS::P, NG = 64 / L, ST = EXIT_STEP;
+    const int p = CTL(C->round) & 1;
+    const int32_t nch = CTL(C->lst[p].chunks);
+    const uint64_t *sig = sel(R.sig, CTL(C->cur));
+    const int32_t *ids = sel(R.f_ids, p);
+    const Chunk *chunks = sel(R.chunks, p);
+    const int ln = lane_id(), sub = ln % L, grp = ln / L;
+    const int64_t wave = (bid * (int64_t)BLOCK + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)nb * BLOCK) >> 6;
+    uint64_t lvp[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) lvp[k] = CTL(C->live[sub * P + k]);
+    for (int64_t c = wave; c < nch; c += nwaves) {   // wave-uniform
+        const Chunk cd = chunks[c];
+        const int32_t u = ids[cd.entry];
+        uint64_t have[P], acc[P];
+        bool lack = false;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            const int64_t o = (int64_t)u * W + sub * P + k;
+            have[k] = sig[o] | CTL(R.acc[o]);
+            acc[k] = 0;
+            lack |= (lvp[k] & ~have[k]) != 0;
+        }
+        if (__ballot(lack) == 0) continue;
+        const int64_t b = g.rp[u] + cd.off, lim = g.rp[u + 1];
+        const int64_t e = b + EXIT_CHUNK < lim ? b + EXIT_CHUNK : lim;
+        for (int64_t a0 = b + grp; a0 - grp < e; a0 += NG * ST) {   // wave-uniform
+            int32_t v[ST];
+#pragma unroll
+            for (int q = 0; q < ST; ++q) v[q] = a0 + q * NG < e ? g.col[a0 + q * NG] : -1;
+#pragma unroll
+            for (int q = 0; q < ST; ++q) {
+                if (v[q] < 0) continue;
+                uint64_t row[P];
+                load_row<P>(sig + (int64_t)v[q] * W + sub * P, row);
+#pragma unroll
+                for (int k = 0; k < P; ++k) acc[k] |= row[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+#pragma unroll
+            for (int o = 32; o >= L; o >>= 1) acc[k] |= __shfl_xor(acc[k], o);
+            const uint64_t add = acc[k] & ~have[k];
+            if (grp == 0 && add)
+                atomicOr((unsigned long long *)&R.acc[(int64_t)u * W + sub * P + k], (unsigned long long)add);
+        }
+    }
+}
+
+// High-degree nodes of a pull round: the chunks left their ORed rows in the
+// accumulator.  After an early-exit pull (EXIT) the same for the nodes it left
+// to chunks (the round's list).
+template <int W>
+PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb, int64_t *parts = nullptr,
+                            const int32_t *hub_node = nullptr, int nhubs = 0) {
+    Ctrl *C = R.ctrl;
+    if (nhubs == 0) {
         if (parts && threadIdx.x == 0) {
             PUT(parts[0 * POST_MAX + bid], (int64_t)0);
             PUT(parts[1 * POST_MAX + bid], (int64_t)0);
@@ -1030,7 +1351,8 @@ PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb,
     uint32_t sc[W];
 #pragma unroll
     for (int k = 0; k < W; ++k) sc[k] = 0;
-    const int64_t items = (int64_t)g.nhubs * W;
+    uint64_t gm = 0;
+    const int64_t items = (int64_t)nhubs * W;
     const int64_t stride = (int64_t)nb * BLOCK;
     for (int64_t base = bid * (int64_t)BLOCK + (threadIdx.x & ~63); base < items; base += stride) {
         const int64_t idx = base + ln;
@@ -1038,7 +1360,7 @@ PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb,
         uint64_t nw = 0;
         int32_t u = 0;
         if (valid) {
-            u = g.hub_node[idx / W];
+            u = hub_node[idx / W];
             const int64_t o = (int64_t)u * W + w;
             const uint64_t av = R.acc[o];
             R.acc[o] = 0;
@@ -1055,6 +1377,7 @@ PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb,
             R.stamp[u] = r;
         }
         const int pc = __popcll(nw);
+        gm |= nw;
         if (R.G == 1) {
             pop += (uint64_t)pc;
             if (per_seed) seed_ballot<W>(nw, sc);
@@ -1064,6 +1387,7 @@ PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb,
             if (per_seed) seed_bits_keyed<W>(R, r, gi, nw, valid);
         }
     }
+    if (g.exit_ok) add_gain<W>(C, gm);
     __shared__ unsigned long long s_red[BLOCK / 64];
     const unsigned long long tp = block_sum<unsigned long long>(pop, s_red);
     const unsigned long long tn = block_sum<unsigned long long>((unsigned long long)nodes, s_red);
@@ -1711,6 +2035,7 @@ PP_DEV void phase_round_end(const GraphDev &g, const RunDev &R, int init, int np
     // closing launch's partials
     long long v[4] = {0, 0, 0, 0};
     if (mode == MODE_PULL) {
+        if (exits(g, C, r)) nparts = exit_blocks(nparts, R.W);
 #pragma unroll 4
         for (int b = threadIdx.x; b < nparts; b += BLOCK) {
             v[0] += R.blk_cnt[b];
@@ -1827,6 +2152,25 @@ PP_DEV void phase_round_end(const GraphDev &g, const RunDev &R, int init, int np
     }
 }
 
+// After a pull's round end (round r), by the same block: the bits the pull
+// found new are the next round's live bits, and a pull that follows exits
+// early when enough pairs are reached for single rows to hold them all.
+PP_DEV void phase_exit_decide(const GraphDev &g, const RunDev &R, int r) {
+    Ctrl *C = R.ctrl;
+    __syncthreads();   // the round end's stores
+    if (threadIdx.x >= 64) return;
+    uint64_t gain = 0;
+    if (threadIdx.x < R.W) {
+        gain = CTL(C->gain[threadIdx.x]);
+        C->live[threadIdx.x] = gain;
+        C->gain[threadIdx.x] = 0;
+    }
+    const int64_t live = wave_sum((int)__popcll(gain));
+    if (threadIdx.x == 0) {
+        C->lst[r & 1] = ListCounts{0, 0};   // what an early-exit pull listed
+        C->exit_round = CTL(C->reached) * EXIT_SHARE >= g.open_nodes * live ? r + 1 : 0;
+    }
+}
 
 // ---------------------------------------------------------------- kernels
 
@@ -1852,7 +2196,10 @@ k_pull(GraphDev g, RunDev R0) {
         if (r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
     }
     if (C->mode == MODE_PULL) {
-        phase_pull<W, KK, false, DEAD>(g, R, blockIdx.x, gridDim.x);
+        if (exits(g, C, C->round)) {
+            const int nb = exit_blocks(gridDim.x, W);
+            if (blockIdx.x < nb) phase_pull_exit<W>(g, R, blockIdx.x, nb);
+        } else phase_pull<W, KK, false, DEAD>(g, R, blockIdx.x, gridDim.x);
     } else if (C->prev_mode == MODE_PULL && blockIdx.x < FRONTIER_BLOCKS) {
         const int nb = gridDim.x < FRONTIER_BLOCKS ? (int)gridDim.x : FRONTIER_BLOCKS;
         phase_frontier<W, 1024>(g, R, blockIdx.x, nb);
@@ -1879,15 +2226,21 @@ k_pull_short(GraphDev g, RunDev R0) {
 }
 template <int W> __global__ void __launch_bounds__(BLOCK) k_push(GraphDev g, RunDev R0) {
     const RunDev R = group_view(R0, blockIdx.y);
-    if (R.ctrl->converged || R.ctrl->mode != MODE_PUSH) return;
-    phase_push<W>(g, R, blockIdx.x, gridDim.x);
+    const int32_t mode = R.ctrl->mode;
+    if (R.ctrl->converged) return;
+    if (mode == MODE_PUSH) phase_push<W>(g, R, blockIdx.x, gridDim.x);
+    else if (mode == MODE_PULL && exits(g, R.ctrl, R.ctrl->round)) phase_pull_rest<W>(g, R, blockIdx.x, gridDim.x);
 }
 // The sparse pull's kernel, apart from the push's so that a run that never
 // takes it keeps the push kernel's smaller register and LDS footprint.
 template <int W> __global__ void __launch_bounds__(BLOCK) k_spull(GraphDev g, RunDev R0) {
     const RunDev R = group_view(R0, blockIdx.y);
-    if (R.ctrl->converged || R.ctrl->mode != MODE_SPULL) return;
-    phase_push<W, true, true>(g, R, blockIdx.x, gridDim.x);
+    const int32_t mode = R.ctrl->mode;
+    if (R.ctrl->converged) return;
+    if (mode == MODE_SPULL) phase_push<W, true, true>(g, R, blockIdx.x, gridDim.x);
+    // the chunks of an early-exit pull, unless the push's kernel is launched too
+    else if (R.sparse_pull == 1 && mode == MODE_PULL && exits(g, R.ctrl, R.ctrl->round))
+        phase_pull_rest<W>(g, R, blockIdx.x, gridDim.x);
 }
 __global__ void __launch_bounds__(BLOCK) k_round_end(GraphDev g, RunDev R0, int init) {
     const RunDev R = group_view(R0, blockIdx.y);
@@ -1971,10 +2324,13 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
     // the blocks this round's items need (every block reads the same count):
     // the rest leave at once and take no ticket, so a small round's end does
     // not wait for the whole grid to count off
-    const int64_t items = mode == MODE_PULL ? (int64_t)g.nhubs * W : (int64_t)CTL(C->lst[CTL(C->round) & 1].nodes) * W;
+    const int r = CTL(C->round), p = r & 1;
+    const bool chunked = mode == MODE_PULL && !exits(g, C, r);   // high-degree nodes; else the round's list
+    const int64_t items = (int64_t)(chunked ? g.nhubs : CTL(C->lst[p].nodes)) * W;
     const int nb = post_blocks(items, (int)gridDim.x);
     if ((int)blockIdx.x >= nb) return;
-    if (mode == MODE_PULL) phase_pull_hubs<W>(g, R, blockIdx.x, nb, R.post_part);
+    if (mode == MODE_PULL)
+        phase_pull_hubs<W>(g, R, blockIdx.x, nb, R.post_part, chunked ? g.hub_node : sel(R.f_ids, p), (int)(items / W));
     else phase_push_commit<W>(g, R, 0, blockIdx.x, nb, R.post_part, mode == MODE_SPULL);
     __shared__ int s_last;
     wait_global_ops();
@@ -1983,6 +2339,7 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
     __syncthreads();
     if (!s_last) return;
     phase_round_end<MLP ? INFER_BLOCK : INFER_NONE>(g, R, 0, g.pull_grid, R.post_part, nb);
+    if (mode == MODE_PULL && g.exit_ok) phase_exit_decide(g, R, r);
 }
 
 // Per-node sums for reach and distance statistics: after the initialisation
@@ -2107,6 +2464,7 @@ PP_DEV void cluster_view(const GraphDev &g, const RunDev &R, const Cluster &cl, 
     gv.nhubs = cl.h1 - cl.h0;
     gv.G = 1;
     gv.pull_grid = cl.nb;
+    gv.exit_ok = 0;
     rv = R;
     rv.G = 1;
     rv.ctrl = R.ctrl + cl.g;
@@ -2205,7 +2563,7 @@ __global__ void __launch_bounds__(BLOCK) k_batch(GraphDev g, RunDev R, const Clu
             if (!cluster_barrier(bar, bid, nb)) break;
             if (lead && stamp) stamp[1] = (int64_t)wall_clock64();
             if (gv.nhubs) {
-                phase_pull_hubs<W>(gv, rv, bid, nb);
+                phase_pull_hubs<W>(gv, rv, bid, nb, nullptr, gv.hub_node, gv.nhubs);
                 if (!cluster_barrier(bar, bid, nb)) break;
             }
         }
