@@ -2293,6 +2293,33 @@ void seq_carve(void *base, int64_t k, int64_t nw, int64_t cap, pp::SeqDev &S, in
     S.cap = (int32_t)cap;
 }
 
+// Seeds in flight on node-major rows when k were asked for: the most of 8, 16,
+// 32, 64, ... 512 that is at most k, so that the rows (2 n of kb / 8 bytes) fit
+// the memory of k one-bit-per-node signature pairs; 0 below eight.
+int seq_rows_seeds(int64_t k) {
+    int kb = 0;
+    for (int b = 8; b <= 64 * pp::SEQ_WORDS && b <= k; b *= 2) kb = b;
+    return kb;
+}
+
+// The same region laid out for node-major rows of kb seeds (never more than
+// seq_region_bytes of k >= kb seeds: every part is a part of that layout, or no
+// larger than one).
+void seq_carve_rows(void *base, int64_t n, int kb, int64_t cap, pp::SeqRows &S, int32_t **dseeds) {
+    auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };
+    char *p = (char *)base;
+    S.row_bytes = kb / 8;
+    S.rows = p;
+    p += up(2 * n * S.row_bytes);
+    S.run = (unsigned long long *)p;
+    p += up(8 * 3 * pp::SEQ_WORDS);
+    S.sum_cnt = (int64_t *)p;
+    p += up(8 * cap);
+    S.examined = (int64_t *)p;
+    p += up(8);
+    *dseeds = (int32_t *)p;
+}
+
 int check_seq_args(pp_graph g, const int32_t *seeds, int32_t s, int32_t concurrent, int64_t *counts, int32_t cap_rounds,
                    int32_t *D) {
     if (!g || !seeds || !counts || !D) return fail(PP_EINVAL, "graph, seeds, counts or D is NULL");
@@ -2371,6 +2398,80 @@ int propagate_s_run(pp_graph g, const int32_t *seeds, int32_t s, const pp::SeqDe
     return PP_OK;
 }
 
+// The propagation on node-major rows, kb seeds in flight, in the region of
+// seq_carve_rows.  Clears what must start at zero; leaves the stream synchronised.
+int propagate_s_rows(pp_graph g, const int32_t *seeds, int32_t s, void *region, int kb, hipStream_t st, int64_t *counts,
+                     int32_t cap_rounds, int32_t *D, int64_t *examined) {
+    pp::SeqRows S{};
+    int32_t *dseeds = nullptr;
+    seq_carve_rows(region, g->n, kb, cap_rounds, S, &dseeds);
+    std::memset(counts, 0, sizeof(int64_t) * (size_t)cap_rounds);
+    counts[0] = s;
+    int32_t dmax = 0;
+    int64_t ex_total = 0;
+    bool overflow = false;
+    const GraphDev gv = graph_view(g, nullptr, 0);
+    std::vector<int32_t> hs((size_t)kb);
+    std::vector<int64_t> hc((size_t)cap_rounds, 0);
+    hipError_t e = hipSuccess;
+    for (int first = 0; first < s && e == hipSuccess; first += kb) {
+        const int kk = std::min(kb, s - first);
+        for (int i = 0; i < kk; ++i) {
+            const int32_t x = seeds[first + i];
+            hs[(size_t)i] = g->perm.empty() ? x : g->perm[(size_t)x];
+        }
+        e = hipMemcpyAsync(dseeds, hs.data(), sizeof(int32_t) * (size_t)kk, hipMemcpyHostToDevice, st);
+        // buffer 0 and the pass log (whole 4-byte words; the rows' last word may
+        // reach into buffer 1, which pass 1 writes in full)
+        const pp::FillSeg segs[] = {{(uint32_t *)S.rows, (g->n * S.row_bytes + 3) / 4, 0u},
+                                    {(uint32_t *)S.sum_cnt, 2 * (int64_t)cap_rounds, 0u}};
+        if (e == hipSuccess) e = pp::launch_fills(segs, 2, st);
+        if (e == hipSuccess) e = pp::launch_seq_rows_seeds(S, dseeds, kk, st);
+        int last = 0, read = 1;   // passes launched; the next pass whose finds the host reads
+        bool running = true;
+        while (running && last + 1 < cap_rounds && e == hipSuccess) {
+            const int upto = std::min(last + 8, cap_rounds - 1);
+            for (int r = last + 1; r <= upto && e == hipSuccess; ++r)
+                e = pp::launch_seq_rows(gv, S, g->seq_heavy, g->nseq_heavy, r, st);
+            last = upto;
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(hc.data() + read, S.sum_cnt + read, sizeof(int64_t) * (size_t)(last + 1 - read),
+                                   hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) break;
+            running = hc[(size_t)last] != 0;   // a pass without a find ends every seed
+            read = last + 1;
+        }
+        int64_t ex = 0;
+        if (e == hipSuccess) e = hipMemcpyAsync(&ex, S.examined, sizeof(ex), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) break;
+        for (int r = 1; r <= last; ++r) {
+            counts[r] += hc[(size_t)r];
+            if (hc[(size_t)r]) dmax = std::max(dmax, r);
+        }
+        overflow |= last == cap_rounds - 1 && last > 0 && hc[(size_t)last] != 0;
+        ex_total += ex;
+    }
+    (void)hipStreamSynchronize(st);   // also after a failed launch: nothing queued still uses the buffers
+    if (e != hipSuccess) return fail(PP_EDEVICE, "PROPAGATE-S: %s", hipGetErrorString(e));
+    *D = dmax;
+    if (examined) *examined = ex_total;
+    if (overflow) return fail(PP_ENOTCONV, "a seed still found nodes at pass %d", cap_rounds - 1);
+    return PP_OK;
+}
+
+// On the region of k seeds: node-major rows from eight seeds on.
+int propagate_s_in(void *region, int64_t k, pp_graph g, const int32_t *seeds, int32_t s, hipStream_t st,
+                   int64_t *counts, int32_t cap_rounds, int32_t *D, int64_t *examined) {
+    if (const int kb = seq_rows_seeds(k))
+        return propagate_s_rows(g, seeds, s, region, kb, st, counts, cap_rounds, D, examined);
+    pp::SeqDev S{};
+    int32_t *dseeds = nullptr;
+    seq_carve(region, k, (g->n + 63) / 64, cap_rounds, S, &dseeds);
+    return propagate_s_run(g, seeds, s, S, dseeds, st, counts, cap_rounds, D, examined);
+}
+
 }  // namespace
 
 extern "C" int pp_propagate_s(pp_graph g, const int32_t *seeds, int32_t s, int32_t concurrent, void *stream,
@@ -2386,11 +2487,8 @@ extern "C" int pp_propagate_s(pp_graph g, const int32_t *seeds, int32_t s, int32
     const int64_t bytes = seq_region_bytes(k, nw, cap_rounds);
     if ((region = pp::dev_malloc((size_t)bytes)) == nullptr)
         return fail(PP_ENOMEM, "PROPAGATE-S: device buffers of %lld bytes", (long long)bytes);
-    pp::SeqDev S{};
-    int32_t *dseeds = nullptr;
-    seq_carve(region, k, nw, cap_rounds, S, &dseeds);
-    rc = propagate_s_run(g, seeds, s, S, dseeds, st, counts, cap_rounds, D, examined);
-    pp::dev_release(region);   // propagate_s_run has synchronised the stream
+    rc = propagate_s_in(region, k, g, seeds, s, st, counts, cap_rounds, D, examined);
+    pp::dev_release(region);   // the propagation has synchronised the stream
     return rc;
 }
 
@@ -2423,8 +2521,5 @@ extern "C" int pp_propagate_s_noalloc(pp_graph g, const int32_t *seeds, int32_t 
     void *region = nullptr;
     if ((rc = pp::noalloc_region(&region)) != PP_OK) return rc;
     hipStream_t st = stream ? (hipStream_t)stream : g->stream;
-    pp::SeqDev S{};
-    int32_t *dseeds = nullptr;
-    seq_carve(region, k, nw, cap_rounds, S, &dseeds);
-    return propagate_s_run(g, seeds, s, S, dseeds, st, counts, cap_rounds, D, examined);
+    return propagate_s_in(region, k, g, seeds, s, st, counts, cap_rounds, D, examined);
 }

@@ -319,6 +319,23 @@ struct SeqDev {
     int32_t k, cap;
     int64_t nw;           // 64-bit words per signature
 };
+// The same on node-major rows: row_bytes * 8 seeds in flight, a row of bits per
+// node (1, 2, 4 or 8 bytes, or 2, 4 or 8 eight-byte words).
+constexpr int SEQ_WORDS = 8;
+#ifndef PP_SEQ_BLOCKS
+#define PP_SEQ_BLOCKS 2048
+#endif
+constexpr int SEQ_BLOCKS = PP_SEQ_BLOCKS;   // at most, for each of the two kinds of lists
+struct SeqRows {
+    void *rows;                // [2][n] rows
+    unsigned long long *run;   // [3][SEQ_WORDS] seeds that found a node in pass r (slot r % 3; pass 0: every seed)
+    int64_t *sum_cnt;          // [cap] nodes found at each pass
+    int64_t *examined;         // [1] arcs examined
+    int32_t row_bytes, pad;
+};
+hipError_t launch_seq_rows_seeds(const SeqRows &S, const int32_t *seeds, int kk, hipStream_t st);
+hipError_t launch_seq_rows(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int r,
+                           hipStream_t st);
 hipError_t launch_seq_seeds(const SeqDev &S, const int32_t *seeds, int kk, hipStream_t st);
 // The current device's address of the fixed PP_NOALLOC_BYTES region that
 // pp_propagate_s_noalloc carves its buffers from (looked up once per device).

@@ -14,6 +14,11 @@
 // not the word that holds it.  Each pass counts, per seed, the nodes it found and
 // the arcs it examined (up to and including the first hit of each node); a
 // seed is done at its first pass that finds nothing.
+//
+// That form serves one to seven seeds in flight.  From eight on the same
+// passes run on node-major rows of one bit per seed (k_seq_rows), which walk
+// each node's list once for all of its seeds; below eight a row of a byte
+// would not fit the memory promised (one bit per node, seed and buffer).
 #include <mutex>
 
 #include "pp_internal.h"
@@ -215,6 +220,285 @@ __global__ void __launch_bounds__(BLOCK) k_seq_end(SeqDev S, int r) {
     __shared__ long long s_red[BLOCK / 64];
     const long long t = block_total<long long>(sum, s_red);
     if (threadIdx.x == 0 && t) atomicAdd((unsigned long long *)&S.sum_cnt[r], (unsigned long long)t);
+}
+
+// ---------------------------------------------------------------- node-major rows
+
+namespace {
+
+template <typename T, int P> PS_DEV void load_slice(const T *p, T (&v)[P]) {
+    if constexpr (P == 2) {
+        const ulonglong2 q = *reinterpret_cast<const ulonglong2 *>(p);
+        v[0] = q.x;
+        v[1] = q.y;
+    } else {
+        v[0] = p[0];
+    }
+}
+
+template <typename T, int P> PS_DEV void store_slice(T *p, const T (&v)[P]) {
+    if constexpr (P == 2) {
+        ulonglong2 q;
+        q.x = v[0];
+        q.y = v[1];
+        *reinterpret_cast<ulonglong2 *>(p) = q;
+    } else {
+        p[0] = v[0];
+    }
+}
+
+template <typename T, int P> PS_DEV bool any_bit(const T (&v)[P]) {
+    T o = 0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) o |= v[k];
+    return o != 0;
+}
+
+template <typename T, int P> PS_DEV int bits(const T (&v)[P]) {
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) c += __popcll((unsigned long long)v[k]);
+    return c;
+}
+
+template <typename T> PS_DEV T from_lane(T v, int lane_) {
+    if constexpr (sizeof(T) == 8) return (T)__shfl((unsigned long long)v, lane_);
+    else return (T)__shfl((unsigned int)v, lane_);
+}
+
+}  // namespace
+
+// Pass r of every seed in flight on rows of W words of type T (bit i: seed i).
+// A node's pending bits are the running seeds that have not reached it; its
+// list is walked in order, each arc adds one examined arc per pending bit and
+// clears the bits of its successor's row, and the walk ends when none is left:
+// each seed's early break at its own first hit, counted as if it walked alone.
+// The first heavy_blocks blocks take the nodes with more than SEQ_LIGHT
+// successors, one per wave: its groups of L lanes (16 bytes of a row per lane)
+// gather SEQ_STEP consecutive arcs each, and an exclusive prefix OR over the
+// groups gives every group the bits still pending at its first arc.  The other
+// blocks take the rest, one node per group.  Every node's row goes to the next
+// buffer.
+// Bound by the gathers of a dense round (one row per arc serves every seed),
+// like the pull of PROPAGATE-P; the seed-major form gathers a word per arc and
+// seed.  R-MAT 20, 256 seeds, per call: 22.8 ms seed-major (two launches of
+// passes, 22.1 ms in them), 1.22 ms here (1.14 ms in the passes).
+constexpr int SEQ_STEP = 4;
+template <typename T, int W>
+__global__ void __launch_bounds__(BLOCK) k_seq_rows(GraphDev g, SeqRows S, const int32_t *heavy, int64_t nheavy, int r,
+                                                   int heavy_blocks) {
+    constexpr int L = W >= 2 ? W / 2 : 1;   // lanes per row
+    constexpr int P = W / L;                // words per lane
+    constexpr int NG = 64 / L;              // groups per wave
+    constexpr int ST = SEQ_STEP;
+    const T *cur = (const T *)S.rows + (int64_t)((r - 1) & 1) * g.n * W;
+    T *nxt = (T *)S.rows + (int64_t)(r & 1) * g.n * W;
+    const unsigned long long *run = S.run + ((r - 1) % 3) * SEQ_WORDS;   // the seeds that found a node in pass r - 1
+    unsigned long long *found_by = S.run + (r % 3) * SEQ_WORDS;
+    if (blockIdx.x == 0 && threadIdx.x < SEQ_WORDS) S.run[((r + 1) % 3) * SEQ_WORDS + threadIdx.x] = 0;
+    const int ln = lane(), sub = ln % L, grp = ln / L, wv = threadIdx.x >> 6;
+    T rn[P];
+    bool open_seeds = false;
+#pragma unroll
+    for (int w = 0; w < W; ++w) open_seeds |= run[w] != 0;
+    if (!open_seeds) return;   // every seed is done
+#pragma unroll
+    for (int k = 0; k < P; ++k) rn[k] = (T)run[sub * P + k];
+    int64_t found = 0, exam = 0;
+    T gain[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) gain[k] = 0;
+
+    if ((int)blockIdx.x < heavy_blocks) {
+        const int64_t nw = (int64_t)heavy_blocks * (BLOCK / 64);
+        for (int64_t h = (int64_t)blockIdx.x * (BLOCK / 64) + wv; h < nheavy; h += nw) {   // wave-uniform
+            const int32_t u = heavy[h];
+            int64_t a = g.rp[u];
+            const int64_t e = g.rp[u + 1];
+            T row[P], pend[P];
+            load_slice<T, P>(cur + (int64_t)u * W + sub * P, row);
+#pragma unroll
+            for (int k = 0; k < P; ++k) pend[k] = rn[k] & (T)~row[k];
+            int32_t v[ST];
+#pragma unroll
+            for (int q = 0; q < ST; ++q) v[q] = a + grp * ST + q < e ? g.col[a + grp * ST + q] : -1;
+            while (a < e && __ballot(any_bit<T, P>(pend))) {   // wave-uniform
+                T rows[ST][P];
+#pragma unroll
+                for (int q = 0; q < ST; ++q) {
+                    if (v[q] >= 0) {
+                        load_slice<T, P>(cur + (int64_t)v[q] * W + sub * P, rows[q]);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < P; ++k) rows[q][k] = 0;
+                    }
+                }
+                const int64_t left = e - (a + grp * ST);   // arcs from the group's first on
+                a += NG * ST;
+#pragma unroll
+                for (int q = 0; q < ST; ++q) v[q] = a + grp * ST + q < e ? g.col[a + grp * ST + q] : -1;
+                T p[P];
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    T o = 0;
+#pragma unroll
+                    for (int q = 0; q < ST; ++q) o |= rows[q][k];
+#pragma unroll
+                    for (int d = L; d < 64; d <<= 1) {   // inclusive prefix OR over the groups
+                        const T t = from_lane<T>(o, ln - d < 0 ? ln : ln - d);
+                        o |= t;
+                    }
+                    const T before = from_lane<T>(o, ln < L ? ln : ln - L);
+                    p[k] = pend[k] & (T)~(ln < L ? (T)0 : before);
+                    pend[k] &= (T)~from_lane<T>(o, 64 - L + sub);
+                }
+#pragma unroll
+                for (int q = 0; q < ST; ++q) {
+                    if (q < left) exam += bits<T, P>(p);
+#pragma unroll
+                    for (int k = 0; k < P; ++k) p[k] &= (T)~rows[q][k];
+                }
+            }
+            if (grp == 0) {
+                T nb[P];
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    nb[k] = rn[k] & (T)~row[k] & (T)~pend[k];
+                    row[k] |= nb[k];
+                    gain[k] |= nb[k];
+                }
+                found += bits<T, P>(nb);
+                store_slice<T, P>(nxt + (int64_t)u * W + sub * P, row);
+            }
+        }
+    } else {
+        const int64_t nw = (int64_t)(gridDim.x - heavy_blocks) * (BLOCK / 64);
+        const int64_t first = (int64_t)(blockIdx.x - heavy_blocks) * (BLOCK / 64) + wv;
+        for (int64_t u0 = first * NG; u0 < g.n; u0 += nw * NG) {   // wave-uniform
+            const int64_t u = u0 + grp;
+            int64_t a = 0;
+            int64_t left = 0;
+            bool mine = u < g.n;
+            T row[P], pend[P];
+#pragma unroll
+            for (int k = 0; k < P; ++k) row[k] = 0;
+            if (mine) {
+                a = g.rp[u];
+                left = g.rp[u + 1] - a;
+                load_slice<T, P>(cur + u * W + sub * P, row);
+            }
+            mine = mine && left <= SEQ_LIGHT;
+#pragma unroll
+            for (int k = 0; k < P; ++k) pend[k] = mine ? (T)(rn[k] & (T)~row[k]) : (T)0;
+            while (true) {   // wave-uniform exit
+                const uint64_t m = __ballot(any_bit<T, P>(pend) && left > 0);
+                if (m == 0) break;
+                const bool go = ((m >> (ln - sub)) & ((1ull << L) - 1ull)) != 0;   // any lane of the group
+                int32_t v[ST];
+#pragma unroll
+                for (int q = 0; q < ST; ++q) v[q] = go && q < left ? g.col[a + q] : -1;
+                T rows[ST][P];
+#pragma unroll
+                for (int q = 0; q < ST; ++q) {
+                    if (v[q] >= 0) {
+                        load_slice<T, P>(cur + (int64_t)v[q] * W + sub * P, rows[q]);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < P; ++k) rows[q][k] = 0;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < ST; ++q) {
+                    if (v[q] >= 0) exam += bits<T, P>(pend);
+#pragma unroll
+                    for (int k = 0; k < P; ++k) pend[k] &= (T)~rows[q][k];
+                }
+                a += ST;
+                left -= ST;
+            }
+            if (mine) {
+                T nb[P];
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    nb[k] = rn[k] & (T)~row[k] & (T)~pend[k];
+                    row[k] |= nb[k];
+                    gain[k] |= nb[k];
+                }
+                found += bits<T, P>(nb);
+                store_slice<T, P>(nxt + u * W + sub * P, row);
+            }
+        }
+    }
+    // the block's sums; a seed that found a node runs on (bits only get set, so
+    // a block whose bits are all there adds nothing)
+    __shared__ long long s_red[BLOCK / 64];
+    __shared__ unsigned long long s_gain[SEQ_WORDS];
+    if (threadIdx.x < SEQ_WORDS) s_gain[threadIdx.x] = 0;
+    const long long tf = block_total<long long>(found, s_red);   // its barriers order the clears
+    const long long te = block_total<long long>(exam, s_red);
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        unsigned long long o = (unsigned long long)gain[k];
+#pragma unroll
+        for (int d = 32; d >= L; d >>= 1) o |= __shfl_xor(o, d);
+        if (grp == 0 && o) atomicOr(&s_gain[sub * P + k], o);
+    }
+    __syncthreads();
+    if (threadIdx.x < W) {
+        const unsigned long long o = s_gain[threadIdx.x];
+        if (o & ~__hip_atomic_load(&found_by[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicOr(&found_by[threadIdx.x], o);
+    }
+    if (threadIdx.x == 0) {
+        if (tf) atomicAdd((unsigned long long *)&S.sum_cnt[r], (unsigned long long)tf);
+        if (te) atomicAdd((unsigned long long *)S.examined, (unsigned long long)te);
+    }
+}
+
+// Seed j of the batch (kk of them) starts with its own bit, in buffer 0
+// (cleared before); the running seeds of pass 1 are all of them.
+__global__ void __launch_bounds__(BLOCK) k_seq_rows_seeds(SeqRows S, const int32_t *seeds, int kk) {
+    const int W32 = S.row_bytes / 4;   // 32-bit words per row (a narrower row: part of one)
+    for (int j = threadIdx.x; j < kk; j += BLOCK) {
+        const int64_t byte = (int64_t)seeds[j] * S.row_bytes + (W32 ? (j >> 5) * 4 : 0);
+        const int bit = W32 ? j & 31 : j + 8 * (int)(byte & 3);   // a narrow row lies inside its 4-byte word
+        atomicOr((unsigned int *)S.rows + (byte >> 2), 1u << bit);
+    }
+    for (int w = threadIdx.x; w < 3 * SEQ_WORDS; w += BLOCK) {
+        const int lo = w * 64;   // seeds of word w of the first mask
+        const int c = w < SEQ_WORDS ? (kk - lo < 0 ? 0 : (kk - lo > 64 ? 64 : kk - lo)) : 0;
+        S.run[w] = c == 64 ? ~0ull : (1ull << c) - 1ull;
+    }
+    if (threadIdx.x == 0) *S.examined = 0;
+}
+
+hipError_t launch_seq_rows_seeds(const SeqRows &S, const int32_t *seeds, int kk, hipStream_t st) {
+    hipLaunchKernelGGL(k_seq_rows_seeds, dim3(1), dim3(BLOCK), 0, st, S, seeds, kk);
+    return hipGetLastError();
+}
+
+template <typename T, int W>
+static hipError_t seq_rows_impl(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int r,
+                                hipStream_t st) {
+    constexpr int NG = 64 / (W >= 2 ? W / 2 : 1);
+    const int64_t hb = (nheavy + BLOCK / 64 - 1) / (BLOCK / 64), lb = (g.n + NG * (BLOCK / 64) - 1) / (NG * (BLOCK / 64));
+    const int nh = (int)(hb < SEQ_BLOCKS ? hb : SEQ_BLOCKS), nl = (int)(lb < SEQ_BLOCKS ? lb : SEQ_BLOCKS);
+    hipLaunchKernelGGL((k_seq_rows<T, W>), dim3(nh + nl), dim3(BLOCK), 0, st, g, S, heavy, nheavy, r, nh);
+    return hipGetLastError();
+}
+
+hipError_t launch_seq_rows(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int r,
+                           hipStream_t st) {
+    switch (S.row_bytes) {
+        case 1: return seq_rows_impl<uint8_t, 1>(g, S, heavy, nheavy, r, st);
+        case 2: return seq_rows_impl<uint16_t, 1>(g, S, heavy, nheavy, r, st);
+        case 4: return seq_rows_impl<uint32_t, 1>(g, S, heavy, nheavy, r, st);
+        case 8: return seq_rows_impl<uint64_t, 1>(g, S, heavy, nheavy, r, st);
+        case 16: return seq_rows_impl<uint64_t, 2>(g, S, heavy, nheavy, r, st);
+        case 32: return seq_rows_impl<uint64_t, 4>(g, S, heavy, nheavy, r, st);
+        case 64: return seq_rows_impl<uint64_t, 8>(g, S, heavy, nheavy, r, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // The fixed device region of pp_propagate_s_noalloc: PROPAGATE-S's buffers
