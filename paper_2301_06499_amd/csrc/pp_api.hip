@@ -1674,10 +1674,12 @@ extern "C" int pp_propagate_until_converged(pp_run r, int32_t max_rounds, int64_
                 r->pull_ms[(size_t)(before + i)] += ms;
             }
         }
-        if (r->opt.rounds_per_sync <= 0) K = std::min(std::max(8, r->host_ctrl.round - start), 64);
+        if (r->opt.rounds_per_sync <= 0) K = std::min(std::max(8, launched), 64);
     }
     // results, from what the waits above copied back
-    const int last = std::min(r->host_ctrl.round, r->cap - 1);
+    // (the round about to run has no row yet: reading it now would keep its
+    // zeros when the propagation goes on)
+    const int last = std::min(r->host_ctrl.converged ? r->host_ctrl.round : r->host_ctrl.round - 1, r->cap - 1);
     if (counts) {
         int rc = ensure_staged(r, last + 1);
         if (rc) return rc;
