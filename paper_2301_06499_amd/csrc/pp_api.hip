@@ -1594,19 +1594,23 @@ namespace {
 
 hipEvent_t slot_event(pp_run r, int i, int which) { return r->timing ? r->ev[(size_t)(2 * i + which)] : nullptr; }
 
-int launch_batch(pp_run r, int k) {
+// k rounds; light: the light rounds that come first, however many, before them
+// (their number is not bounded by k).
+int launch_batch(pp_run r, int k, bool light) {
     GraphDev gv = graph_view(r->g, run_tiles(r), r->W);
     if (!r->opt.use_graph || (r->timing && !r->graph_events)) {
+        if (light) HIP_TRY(noted(r, pp::launch_light(gv, r->dev, r->stream)));
         for (int i = 0; i < k; ++i)
             HIP_TRY(noted(r, pp::launch_round(gv, r->dev, r->stream, slot_event(r, i, 0), slot_event(r, i, 1))));
         return PP_OK;
     }
-    auto it = r->graphs.find(k);
+    const int key = light ? -k : k;
+    auto it = r->graphs.find(key);
     if (it == r->graphs.end()) {
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
         HIP_TRY(hipStreamBeginCapture(r->stream, hipStreamCaptureModeThreadLocal));
-        hipError_t le = hipSuccess;
+        hipError_t le = light ? pp::launch_light(gv, r->dev, r->stream) : hipSuccess;
         for (int i = 0; i < k && le == hipSuccess; ++i)
             le = pp::launch_round(gv, r->dev, r->stream, slot_event(r, i, 0), slot_event(r, i, 1));
         hipError_t ce = hipStreamEndCapture(r->stream, &graph);
@@ -1615,14 +1619,14 @@ int launch_batch(pp_run r, int k) {
             if (graph) (void)hipGraphDestroy(graph);
             (void)hipGetLastError();
             r->graph_events = false;
-            return launch_batch(r, k);
+            return launch_batch(r, k, light);
         }
         if (le != hipSuccess) return fail(PP_EDEVICE, "round capture: %s", hipGetErrorString(le));
         if (ce != hipSuccess) return fail(PP_EDEVICE, "end capture: %s", hipGetErrorString(ce));
         HIP_TRY(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
-        r->graph_defs[k] = graph;
-        r->graphs[k] = exec;
-        it = r->graphs.find(k);
+        r->graph_defs[key] = graph;
+        r->graphs[key] = exec;
+        it = r->graphs.find(key);
     }
     HIP_TRY(noted(r, hipGraphLaunch(it->second, r->stream)));
     return PP_OK;
@@ -1636,10 +1640,14 @@ extern "C" int pp_propagate_until_converged(pp_run r, int32_t max_rounds, int64_
     if (counts && cap_rounds < 1) return fail(PP_EINVAL, "cap_rounds < 1");
     const int G = r->G;
     const int limit = (max_rounds > 0 && max_rounds < r->cap - 1) ? max_rounds : r->cap - 1;
-    // adaptive batches: 8 rounds, then as many rounds as have run so far (at
+    // adaptive batches: 8 rounds, then as many as have been launched so far (at
     // most 64) -- a host check costs about as much as a few replayed rounds
     // that find the run converged and return at once
-    const int start = r->host_ctrl.round;
+    int launched = 0;
+    // light rounds first where the propagation may run to the log's end and no
+    // figures of single launches are asked for (the device checks each round)
+    const bool light = limit == r->cap - 1 && G == 1 && !r->timing && !r->dev.node_acc && !r->dev.sparse_pull &&
+                       r->g->m < (int64_t)1 << 32 && r->opt.scheduler != PP_SCHED_PULL;
     int K = r->opt.rounds_per_sync > 0 ? r->opt.rounds_per_sync : 8;
     if (r->pgrid && !r->host_ctrl.converged && r->host_ctrl.round <= limit) {
         int rc = run_persistent(r, limit);
@@ -1655,8 +1663,9 @@ extern "C" int pp_propagate_until_converged(pp_run r, int32_t max_rounds, int64_
             k = p;
         }
         const int before = r->host_ctrl.round;
-        int rc = launch_batch(r, k);
+        int rc = launch_batch(r, k, light);
         if (rc) return rc;
+        launched += k;
         if ((rc = sync_state(r, before + k))) return rc;
         if (r->timing) {
             // rounds before..last ran; launches after convergence returned at once

@@ -372,6 +372,9 @@ enum SparseKinds : int { SPARSE_BY_RUN = 0, SPARSE_PUSH = 1, SPARSE_PULL = 2, SP
 // One round; when e0/e1 are given they are recorded around the pull launch.
 hipError_t launch_round(const GraphDev &g, const RunDev &r, hipStream_t st, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr, int kinds = SPARSE_BY_RUN);
+// The light rounds at the head of a batch (one graph, no round limit below the
+// log's capacity, rounds not timed one by one).
+hipError_t launch_light(const GraphDev &g, const RunDev &r, hipStream_t st);
 // Rounds up to max_round of every graph in one cooperative launch of `grid`
 // blocks split into clusters (device array), initialising graphs at round 0.
 hipError_t launch_batch_persistent(const GraphDev &g, const RunDev &r, const Cluster *clusters, int nclusters,

@@ -2152,6 +2152,350 @@ PP_DEV void phase_round_end(const GraphDev &g, const RunDev &R, int init, int np
     }
 }
 
+// ---------------------------------------------------------------- light rounds
+
+// Capacities of the light rounds (below) in LDS: H slots of the table of nodes
+// that gain bits in a round, which is also the most arcs a round may push, and
+// LC entries of the frontier.  At twice these a round in one block takes as
+// long as three launches (6400 arcs of one word: 27 against 21 us); the
+// persistent loop's are half as large so that two of its blocks still fit a
+// compute unit.
+template <int W, int NT> struct LightShape {
+    static constexpr int H = (NT > BLOCK ? 4096 : 2048) / W;
+    static constexpr int LC = H / 2;
+};
+
+// Whether the round about to run, of a single graph, can be a light one: a push
+// over direct slots whose frontier and arcs fit.
+template <int W, int NT> PP_DEV bool light_ok(const GraphDev &g, const RunDev &R, const Ctrl *C) {
+    if (R.sparse_pull || R.node_acc || g.G != 1 || g.m >= (int64_t)1 << 32) return false;
+    const int p = (CTL(C->round) - 1) & 1;
+    return CTL(C->mode) == MODE_PUSH && !(CTL(C->flat) & 1) && CTL(C->lst[p].nodes) <= LightShape<W, NT>::LC &&
+           CTL(C->f_arcs[p]) <= LightShape<W, NT>::H;
+}
+
+// The cost model for one wave with its weights in registers: lane j holds, for
+// unit j % 32 of each hidden layer, half of the inputs' weights (the first half
+// for j < 32), and two weights of output j / 16 (as MlpThread's second wave).
+struct MlpWave {
+    float w1[MLP_IN / 2], b1, w2[MLP_HID / 2], b2, w3[2], b3;
+};
+
+PP_DEV void mlp_load_wave(const float *w, MlpWave &m) {
+    const int j = lane_id(), unit = j & 31, half = j >> 5;
+#pragma unroll
+    for (int i = 0; i < MLP_IN / 2; ++i) m.w1[i] = w[MLP_W1 + unit * MLP_IN + half * (MLP_IN / 2) + i];
+    m.b1 = w[MLP_B1 + unit];
+#pragma unroll
+    for (int i = 0; i < MLP_HID / 2; ++i) m.w2[i] = w[MLP_W2 + unit * MLP_HID + half * (MLP_HID / 2) + i];
+    m.b2 = w[MLP_B2 + unit];
+    m.w3[0] = w[MLP_W3 + (j >> 4) * MLP_HID + 2 * (j & 15)];
+    m.w3[1] = w[MLP_W3 + (j >> 4) * MLP_HID + 2 * (j & 15) + 1];
+    m.b3 = w[MLP_B3 + (j >> 4)];
+}
+
+// The action (as mlp_decide), in every lane; the whole wave calls.
+PP_DEV int32_t mlp_eval_wave(const MlpWave &m, const float (&f)[MLP_IN], uint32_t allow) {
+    const int j = lane_id(), half = j >> 5;
+    float h = 0.0f;
+#pragma unroll
+    for (int i = 0; i < MLP_IN / 2; ++i) h += m.w1[i] * (half ? f[MLP_IN / 2 + i] : f[i]);
+    h += __shfl_xor(h, 32);
+    const float h1 = fmaxf(h + m.b1, 0.0f);   // lanes j and j + 32: unit j % 32
+    h = 0.0f;
+#pragma unroll
+    for (int i = 0; i < MLP_HID / 2; ++i) h += m.w2[i] * __shfl(h1, half * (MLP_HID / 2) + i);
+    h += __shfl_xor(h, 32);
+    const float h2 = fmaxf(h + m.b2, 0.0f);
+    float o = m.w3[0] * __shfl(h2, 2 * (j & 15)) + m.w3[1] * __shfl(h2, 2 * (j & 15) + 1);
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) o += __shfl_xor(o, d);
+    o += m.b3;   // lanes 16 k .. 16 k + 15: output k
+    int32_t best = -1;
+    float bo = 0.0f;
+#pragma unroll
+    for (int a = 0; a < MLP_OUT; ++a) {
+        const float oa = __shfl(o, 16 * a);
+        if (!((allow >> a) & 1u) || best == -2) continue;
+        if (!__builtin_isfinite(oa)) {
+            best = -2;
+            continue;
+        }
+        if (best < 0 || oa < bo) {
+            best = a;
+            bo = oa;
+        }
+    }
+    return best < 0 ? -1 : best;
+}
+
+// Push rounds of a small frontier, one after the other in one block of NT
+// threads, with the frontier (ids, new bits, first arcs) in LDS: each round
+// pushes its frontier's predecessor arcs, flattened over the threads, by atomic
+// ORs on the rows as any push does; the nodes that gained bits and those bits
+// are gathered in an LDS table (open addressing by node id, one slot per node,
+// so a node is queued once), which becomes the next frontier.  Neither the
+// accumulator nor the stamps are touched, and no list goes through memory.
+// Left when the round's successor is no push, is beyond max_round or exceeds
+// the LDS capacities, and at convergence, with the control block, logs and
+// frontier list as the other rounds leave them.
+// What bounds a round is its chain of dependent accesses: predecessor ids, the
+// atomics, the new nodes' offsets; two barriers.  Per round, path of 5000 nodes,
+// 64 seeds: 14.5 us in three launches and 8.4 us in the persistent loop's
+// general phases, 2.8 us here (2.6 us in that loop).  301^2 lattice, per round
+// of up to 512 arcs 12.5 -> 3.2 us, up to 2048 13.1 -> 4.7 us, up to 4096 13.2 ->
+// 7.6 us.  The 64-graph batch, whose longest path runs 19 951 rounds: 189.7 ->
+// 81.6 ms.
+// direct_only: as in phase_round_end.
+template <int W, int NT>
+PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool direct_only) {
+    using LS = LightShape<W, NT>;
+    constexpr int H = LS::H, LC = LS::LC;
+    constexpr int U = 2;   // arcs per thread in flight
+    __shared__ int32_t s_key[H];
+    __shared__ unsigned long long s_val[H * W];
+    __shared__ uint16_t s_map[H];             // frontier entry of each arc
+    __shared__ uint16_t s_slot[H];            // table slots in use, in order of insertion
+    __shared__ uint32_t s_beg[LC];            // first predecessor arc
+    __shared__ int32_t s_start[LC], s_id[LC]; // first flat arc; node
+    __shared__ unsigned long long s_del[LC * W];
+    // by parity of the round: new bits, nodes that gained them, their predecessor arcs
+    __shared__ unsigned long long s_cnt[2], s_arcs[2];
+    __shared__ int32_t s_new[2];
+    __shared__ int32_t s_chunks, s_next;
+    Ctrl *C = R.ctrl;
+    const int tid = threadIdx.x, ln = lane_id();
+    const int w = tid & (W - 1);
+    int r = CTL(C->round);
+    uint64_t *sig = sel(R.sig, CTL(C->cur));
+    int64_t reached = CTL(C->reached), last = CTL(C->last_count);
+    int64_t prev_arcs = CTL(C->f_arcs[(r - 1) & 1]);
+    const int n0 = CTL(C->lst[(r - 1) & 1].nodes);
+    for (int i = tid; i < H; i += NT) s_key[i] = -1;
+    for (int i = tid; i < H * W; i += NT) s_val[i] = 0;
+    if (tid < 2) {
+        s_cnt[tid] = 0;
+        s_arcs[tid] = 0;
+        s_new[tid] = 0;
+    }
+    if (tid == 0) s_chunks = 0;
+    __syncthreads();
+    // entry `slot` (slot < 0: none) of the list of parity q: node id with deg
+    // arcs from beg on; the whole wave calls
+    auto place = [&](int slot, int32_t id, int64_t beg, int deg, int q) {
+        const int incl = wave_inclusive_scan(deg);
+        unsigned long long base = 0;
+        if (ln == 63) base = atomicAdd(&s_arcs[q], (unsigned long long)(uint32_t)incl);
+        base = __shfl(base, 63);
+        const int64_t at = (int64_t)base + incl - deg;
+        const int start = at < H ? (int)at : H;
+        if (slot >= 0) {
+            s_beg[slot] = (uint32_t)beg;
+            s_start[slot] = start;
+            s_id[slot] = id;
+            if (deg <= PUSH_LIGHT)
+                for (int j = 0; j < deg; ++j)
+                    if (start + j < H) s_map[start + j] = (uint16_t)slot;
+        }
+        uint64_t longm = __ballot(slot >= 0 && deg > PUSH_LIGHT);
+        while (longm) {   // a long list: the wave fills its part of the map
+            const int lead = __builtin_ctzll(longm);
+            longm &= longm - 1;
+            const int s0 = __shfl(start, lead), sl = __shfl(slot, lead), sd = __shfl(deg, lead);
+            for (int j = ln; j < sd && s0 + j < H; j += 64) s_map[s0 + j] = (uint16_t)sl;
+        }
+    };
+    {   // the frontier from its list in memory
+        const int q = (r - 1) & 1;
+        const int32_t *ids = sel(R.f_ids, q);
+        const uint64_t *dl = sel(R.f_delta, q);
+        for (int i = tid; i < n0 * W; i += NT) s_del[i] = dl[i];
+        for (int i0 = 0; i0 < n0; i0 += NT) {   // block-uniform
+            const int i = i0 + tid;
+            const bool valid = i < n0;
+            const int32_t id = valid ? ids[i] : 0;
+            const int64_t b = valid ? g.trp[id] : 0, e = valid ? g.trp[id + 1] : 0;
+            place(valid ? i : -1, id, b, (int)(e - b), q);
+        }
+    }
+    const bool log_wave = tid >= NT - 64;   // its lanes run short of arcs first
+    const bool asked = R.sched == PP_SCHED_MLP || R.sched == PP_SCHED_PLAN;   // the next action is not a rule's
+    const uint32_t allow = allowed_actions(R, direct_only);
+    MlpWave mw;
+    if (R.sched == PP_SCHED_MLP && log_wave) mlp_load_wave(R.mlp, mw);
+    if (tid == NT - 64 && r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
+    __syncthreads();
+    while (true) {   // block-uniform; each iteration is round r
+        const int q = r & 1;
+        const int A = (int)s_arcs[q ^ 1];   // at most H
+        const int32_t planned = R.sched == PP_SCHED_PLAN && log_wave && r + 1 < R.cap ? R.plan[r + 1] : -1;
+        uint32_t pop = 0;
+        for (int a0 = 0; a0 < A * W; a0 += NT * U) {
+            int32_t v[U];
+            unsigned long long d[U], old[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int arc = (a0 + u * NT + tid) / W;
+                v[u] = -1;
+                d[u] = 0;
+                if (arc < A) {
+                    const int en = s_map[arc];
+                    v[u] = g.tcol[s_beg[en] + (uint32_t)(arc - s_start[en])];
+                    d[u] = s_del[en * W + w];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                old[u] = d[u] ? atomicOr((unsigned long long *)&sig[(int64_t)v[u] * W + w], d[u]) : 0ull;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                unsigned long long nb = d[u] & ~old[u];
+                if (nb == 0) continue;
+                pop += (uint32_t)__popcll(nb);
+                // the node's slot (at most H insertions into H slots: one is found)
+                uint32_t h = ((uint32_t)v[u] * 2654435761u) >> (32 - __builtin_ctz(H));
+                while (true) {
+                    int32_t kk = s_key[h];
+                    if (kk == -1) {
+                        kk = atomicCAS(&s_key[h], -1, v[u]);
+                        if (kk == -1) {
+                            s_slot[atomicAdd(&s_new[q], 1)] = (uint16_t)h;
+                            break;
+                        }
+                    }
+                    if (kk == v[u]) break;
+                    h = (h + 1) & (H - 1);
+                }
+                atomicOr(&s_val[h * W + w], nb);
+                if (R.seed_counts) {
+                    uint32_t *sc = R.seed_counts + (int64_t)r * R.sstride + w * 64;
+                    for (; nb; nb &= nb - 1) atomicAdd(sc + __builtin_ctzll(nb), 1u);
+                }
+            }
+        }
+        pop = wave_sum(pop);
+        if (ln == 0 && pop) atomicAdd(&s_cnt[q], (unsigned long long)pop);
+        if (tid == NT - 64 && r < R.cap) R.phase_log[(int64_t)r * 3 + 1] = (int64_t)wall_clock64();
+        __syncthreads();
+        const int64_t cnt = (int64_t)s_cnt[q];
+        const int fnodes = s_new[q];
+        const bool fits = fnodes <= LC;   // else the next list goes to memory only
+        int32_t *ids = sel(R.f_ids, q);
+        uint64_t *dl = sel(R.f_delta, q);
+        Chunk *chunks = sel(R.chunks, q);
+        auto add_chunks = [&](int entry, int64_t deg) {
+            const int nch = chunks_for<W>(deg);
+            if (nch == 0) return;
+            const int c0 = atomicAdd(&s_chunks, nch);
+            for (int c = 0; c < nch; ++c) chunks[c0 + c] = Chunk{entry, c * PushShape<W>::CHUNK};
+        };
+        for (int i0 = 0; i0 < fnodes; i0 += NT) {   // block-uniform
+            const int slot = i0 + tid < fnodes ? i0 + tid : -1;
+            int32_t id = 0;
+            int64_t b = 0, e = 0;
+            if (slot >= 0) {
+                const int h = s_slot[slot];
+                id = s_key[h];
+                b = g.trp[id];
+                e = g.trp[id + 1];
+#pragma unroll
+                for (int k = 0; k < W; ++k) {
+                    const unsigned long long x = s_val[h * W + k];
+                    s_val[h * W + k] = 0;
+                    if (fits) s_del[slot * W + k] = x;
+                    else dl[(int64_t)slot * W + k] = x;
+                }
+                s_key[h] = -1;
+                if (!fits) {
+                    ids[slot] = id;
+                    add_chunks(slot, e - b);
+                }
+            }
+            place(fits ? slot : -1, id, b, (int)(e - b), q);
+        }
+        if (tid == 0) {
+            s_cnt[q ^ 1] = 0;
+            s_arcs[q ^ 1] = 0;
+            s_new[q ^ 1] = 0;
+        }
+        __syncthreads();
+        // the round's end (see phase_round_end)
+        const int64_t farcs = (int64_t)s_arcs[q];
+        reached += cnt;
+        float f[MLP_IN];
+        if (log_wave) {
+            sched_features(g, R, r + 1, MODE_PUSH, fnodes, farcs, cnt, reached, last, f);
+            if (asked) {
+                int32_t a = -1;
+                if (R.sched == PP_SCHED_MLP) a = mlp_eval_wave(mw, f, allow);
+                else if (planned >= 0 && planned < MLP_OUT && ((allow >> planned) & 1u)) a = planned;
+                if (tid == NT - 64) s_next = a;
+            }
+            if (tid == NT - 64) {
+                const int64_t now = (int64_t)wall_clock64();
+                R.counts[(int64_t)r * R.cstride] = cnt;
+                R.mode_log[r] = MODE_PUSH;
+                R.arcs_log[r] = prev_arcs;
+                R.phase_log[(int64_t)r * 3 + 2] = now;
+                if (cnt) R.D[0] = r;
+                else R.gconv[0] = 1;
+                if (r + 1 < R.cap) {
+                    if (cnt) R.phase_log[(int64_t)(r + 1) * 3] = now;
+#pragma unroll
+                    for (int i = 0; i < MLP_IN; ++i) R.feat_log[(int64_t)(r + 1) * MLP_IN + i] = f[i];
+                }
+            }
+        }
+        last = cnt;
+        prev_arcs = farcs;
+        if (asked) __syncthreads();   // block-uniform
+        int32_t fl = 0;
+        const int32_t next = take_action(R, r + 1, asked ? s_next : -1, schedule(g, R, r + 1, fnodes, farcs),
+                                         false /* far below PUSH_FILTER_MIN */, direct_only, &fl);
+        const bool full = r + 1 >= R.cap;
+        if (cnt && !full && next == MODE_PUSH && !(fl & 1) && r + 1 <= max_round && fits && farcs <= H) {
+            ++r;
+            continue;
+        }
+        // out: the frontier to its list in memory, the state to the control block
+        if (fits)
+            for (int i = tid; i < fnodes; i += NT) {
+                const int32_t id = s_id[i];
+                ids[i] = id;
+                add_chunks(i, g.trp[id + 1] - g.trp[id]);
+#pragma unroll
+                for (int k = 0; k < W; ++k) dl[(int64_t)i * W + k] = s_del[i * W + k];
+            }
+        __syncthreads();
+        if (tid == NT - 64) {
+            const bool on = cnt && !full;
+            C->acc_pending = 1;
+            C->prev_mode = MODE_PUSH;
+            C->active = cnt ? 1 : 0;
+            C->reached = reached;
+            C->last_count = cnt;
+            C->f_arcs[q] = farcs;
+            C->lst[q] = ListCounts{fnodes, s_chunks};
+#pragma unroll
+            for (int i = 0; i < MLP_IN; ++i) C->feat[i] = f[i];
+            if (!on) {
+                C->round = r;
+                C->converged = 1;
+                if (cnt) C->overflow = 1;
+            } else {
+                C->lst[q ^ 1] = ListCounts{0, 0};
+                C->f_arcs[q ^ 1] = 0;
+                C->mode = next;
+                C->flat = fl;
+                C->round = r + 1;
+            }
+        }
+        __syncthreads();
+        return;
+    }
+}
+static_assert(LightShape<1, 1024>::LC < PUSH_FILTER_MIN, "light rounds leave frontiers of direct slots");
+
 // After a pull's round end (round r), by the same block: the bits the pull
 // found new are the next round's live bits, and a pull that follows exits
 // early when enough pairs are reached for single rows to hold them all.
@@ -2246,6 +2590,16 @@ __global__ void __launch_bounds__(BLOCK) k_round_end(GraphDev g, RunDev R0, int 
     const RunDev R = group_view(R0, blockIdx.y);
     if (R.ctrl->converged) return;
     phase_round_end(g, R, init, g.pull_grid);
+}
+// The light rounds of each seed group at the head of a batch of rounds, as many
+// as come one after the other.
+constexpr int LIGHT_THREADS = 1024;
+template <int W> __global__ void __launch_bounds__(LIGHT_THREADS) k_light(GraphDev g, RunDev R0) {
+    const RunDev R = group_view(R0, blockIdx.y);
+    const Ctrl *C = R.ctrl;
+    // after a pull the frontier is not listed yet
+    if (C->converged || C->prev_mode == MODE_PULL || !light_ok<W, LIGHT_THREADS>(g, R, C)) return;
+    light_rounds<W, LIGHT_THREADS>(g, R, R.cap, false);
 }
 // Algorithm 1's initialisation for a short seed list in one block: the seed
 // bits, the round-0 commit and the round's end, one after the other (the
@@ -2499,7 +2853,8 @@ PP_DEV void cluster_view(const GraphDev &g, const RunDev &R, const Cluster &cl, 
 // read by all of them after a barrier, so they leave together.  Rank 0 logs
 // device-clock stamps per round: [start, after the main phase, end].
 template <int W>
-__global__ void __launch_bounds__(BLOCK) k_batch(GraphDev g, RunDev R, const Cluster *clusters, int nclusters,
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2)))   // two blocks per compute unit
+k_batch(GraphDev g, RunDev R, const Cluster *clusters, int nclusters,
                                                  int max_round) {
     int lo = 0, hi = nclusters - 1;   // cluster holding this block
     while (lo < hi) {
@@ -2552,6 +2907,10 @@ __global__ void __launch_bounds__(BLOCK) k_batch(GraphDev g, RunDev R, const Clu
             if (prev == MODE_PULL) {
                 phase_frontier<W, 256>(gv, rv, bid, nb);
                 if (!cluster_barrier(bar, bid, nb)) break;
+            }
+            if (local && light_ok<W, BLOCK>(gv, rv, C)) {
+                light_rounds<W, BLOCK>(gv, rv, max_round, true);
+                continue;
             }
             phase_push<W, false>(gv, rv, bid, nb);
             if (!cluster_barrier(bar, bid, nb)) break;
@@ -2708,6 +3067,18 @@ hipError_t launch_seed_init(const GraphDev &g, const RunDev &R, const int32_t *s
         case 8: return seed_init_impl<8>(g, R, seeds, map, st);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_light(const GraphDev &g, const RunDev &R, hipStream_t st) {
+    const dim3 grid(1, (unsigned)R.ngroups);
+    switch (R.W) {
+        case 1: hipLaunchKernelGGL(k_light<1>, grid, dim3(LIGHT_THREADS), 0, st, g, R); break;
+        case 2: hipLaunchKernelGGL(k_light<2>, grid, dim3(LIGHT_THREADS), 0, st, g, R); break;
+        case 4: hipLaunchKernelGGL(k_light<4>, grid, dim3(LIGHT_THREADS), 0, st, g, R); break;
+        case 8: hipLaunchKernelGGL(k_light<8>, grid, dim3(LIGHT_THREADS), 0, st, g, R); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_round(const GraphDev &g, const RunDev &R, hipStream_t st, hipEvent_t e0, hipEvent_t e1, int kinds) {
