@@ -1709,45 +1709,41 @@ int copy_signatures(pp_run r, uint64_t *dst, hipMemcpyKind kind);
 extern "C" int pp_get_signatures(pp_run r, uint64_t *dst, int32_t dst_on_device) {
     if (!r || !dst) return fail(PP_EINVAL, "run or dst is NULL");
     if (r->grouped) {
-        // the groups' rows in the caller's bit order (stored node order), then by input id
+        // the groups' rows in the caller's bit order, by input id
         int rc = sync_ctrl(r);   // each group's current buffer
         if (rc) return rc;
         const int64_t n = r->g->n, words = n * r->Wout;
         std::vector<int32_t> cur(r->cur.begin(), r->cur.end());
-        uint64_t *tmp = nullptr, *out = nullptr;
-        const bool direct = dst_on_device && !r->g->perm_d;
-        if (!direct) rc = dev_alloc(&tmp, words);
-        if (!rc && !dst_on_device && r->g->perm_d) rc = dev_alloc(&out, words);
+        uint64_t *tmp = nullptr;
+        if (!dst_on_device) rc = dev_alloc(&tmp, words);
         hipError_t e = hipSuccess;
         if (!rc) e = hipMemcpyAsync(r->dcur, cur.data(), sizeof(int32_t) * cur.size(), hipMemcpyHostToDevice, r->stream);
-        uint64_t *rows = direct ? dst : tmp;
         if (!rc && !e)
-            e = pp::launch_sig_regroup(r->dev.sig[0], n, r->W, r->Wout, r->s, r->sg, r->dcur, r->dpos, r->g->node_graph,
-                                       rows, r->stream);
-        if (!rc && !e && r->g->perm_d) {
-            uint64_t *by_id = dst_on_device ? dst : out;
-            e = pp::launch_gather_rows(by_id, rows, r->g->perm_d, n, r->Wout, r->stream);
-            rows = by_id;
-        }
+            e = pp::launch_sig_regroup(r->dev.sig[0], n, r->W, r->Wout, r->s, r->sg, r->k, r->dcur, r->dpos,
+                                       r->g->node_graph, r->g->perm_d, dst_on_device ? dst : tmp, r->stream);
         if (!rc && !e && !dst_on_device)
-            e = hipMemcpyAsync(dst, rows, sizeof(uint64_t) * (size_t)words, hipMemcpyDeviceToHost, r->stream);
+            e = hipMemcpyAsync(dst, tmp, sizeof(uint64_t) * (size_t)words, hipMemcpyDeviceToHost, r->stream);
         if (!rc && !e) e = hipStreamSynchronize(r->stream);
-        if (rc || e) (void)hipStreamSynchronize(r->stream);   // queued work done before the blocks go back
+        if (rc || e) (void)hipStreamSynchronize(r->stream);   // queued work done before the block goes back
         dev_free(tmp);
-        dev_free(out);
         if (rc) return rc;
         if (e) return fail(PP_EDEVICE, "signature regroup: %s", hipGetErrorString(e));
         return PP_OK;
     }
     if (r->g->perm_d) {
-        // stored order -> input order: assemble the rows, then gather them by id
+        // stored order -> input order: the current rows gathered by id, straight
+        // from the run's buffer (a clustered batch's graphs sit in either buffer:
+        // their rows are assembled first)
         const int64_t words = r->g->n * r->W;
+        const bool one = r->cur.size() <= 1;
         uint64_t *tmp = nullptr, *out = nullptr;
-        int rc = dev_alloc(&tmp, words);
+        int rc = one ? PP_OK : dev_alloc(&tmp, words);
         if (!rc && !dst_on_device) rc = dev_alloc(&out, words);
-        if (!rc) rc = copy_signatures(r, tmp, hipMemcpyDeviceToDevice);
+        if (!rc && !one) rc = copy_signatures(r, tmp, hipMemcpyDeviceToDevice);
         hipError_t e = hipSuccess;
-        if (!rc) e = pp::launch_gather_rows(dst_on_device ? dst : out, tmp, r->g->perm_d, r->g->n, r->W, r->stream);
+        if (!rc)
+            e = pp::launch_gather_rows(dst_on_device ? dst : out, one ? r->dev.sig[r->host_ctrl.cur & 1] : tmp,
+                                       r->g->perm_d, r->g->n, r->W, r->stream);
         if (!rc && !e && !dst_on_device)
             e = hipMemcpyAsync(dst, out, sizeof(uint64_t) * (size_t)words, hipMemcpyDeviceToHost, r->stream);
         if (!rc && !e) e = hipStreamSynchronize(r->stream);

@@ -360,9 +360,11 @@ hipError_t launch_gather_rows(uint64_t *dst, const uint64_t *src, const int32_t 
 // position of the caller's seed i (see k_seed_order).
 hipError_t launch_seed_order(const GraphDev &g, const int32_t *seeds, const int32_t *map, int G, int s_all,
                              int by_reach, int32_t *out, int32_t *pos, hipStream_t st);
-// Rows of a grouped run's signatures in the caller's bit order (stored node order).
-hipError_t launch_sig_regroup(const uint64_t *sig, int64_t n, int Wg, int Wout, int s_all, int sg, const int32_t *cur,
-                              const int32_t *pos, const int32_t *node_graph, uint64_t *out, hipStream_t st);
+// A grouped run's k groups' signatures in the caller's bit order, row x of out
+// the stored node perm[x]'s (perm NULL: x's).
+hipError_t launch_sig_regroup(const uint64_t *sig, int64_t n, int Wg, int Wout, int s_all, int sg, int k,
+                              const int32_t *cur, const int32_t *pos, const int32_t *node_graph, const int32_t *perm,
+                              uint64_t *out, hipStream_t st);
 // seeds: device-readable ids; map (may be NULL): input id -> stored id.
 hipError_t launch_seed_init(const GraphDev &g, const RunDev &r, const int32_t *seeds, const int32_t *map,
                             hipStream_t st);

@@ -561,30 +561,70 @@ __global__ void __launch_bounds__(BLOCK) k_seed_order(GraphDev g, const int32_t 
     }
 }
 
-// Signature rows in the caller's bit order from the rows of a run's seed
-// groups: word j of row u holds the caller's seeds 64 j .. 64 j + 63 of u's
-// graph; seed i sits at internal position q = pos[gi * s_all + i], bit q % sg
-// of group q / sg's row (group grp's current buffer is cur[grp]; each group
-// holds a pair of [n][Wg] buffers, the groups one after another).  Rows in
-// stored order.
+// Signature rows in the caller's bit order and node order from the rows of a
+// run's seed groups: word j of row x holds the caller's seeds 64 j .. 64 j + 63
+// of x's graph; seed i sits at internal position q = pos[gi * s_all + i], bit
+// q % sg of group q / sg's row (group grp's current buffer is cur[grp]; each
+// group holds a pair of [n][Wg] buffers, the groups one after another), and
+// input node x at row perm[x] (perm NULL: x).
+// A block takes RG_NODES nodes, one per thread: their words of every group go
+// through LDS, RG_WORDS at a time, laid out so that a wave reads one word of 64
+// nodes at once; the bit's place is the same for a whole wave of a single graph,
+// so it comes from a table in LDS.  Bound by those LDS reads, one per output bit
+// and node, and by the row gathers: R-MAT 20, two groups of two words: 420 us
+// reading every bit's word from memory, and 21 us to order the rows, before;
+// 127 us here, both in one.
+constexpr int RG_NODES = BLOCK;
+constexpr int RG_WORDS = 16;    // words of a node in LDS at once (32 KB a block)
 __global__ void __launch_bounds__(BLOCK) k_sig_regroup(const uint64_t *sig, int64_t n, int Wg, int Wout, int s_all,
-                                                       int sg, const int32_t *cur, const int32_t *pos,
-                                                       const int32_t *node_graph, uint64_t *out) {
-    const int64_t total = n * Wout;
-    for (int64_t t = blockIdx.x * (int64_t)BLOCK + threadIdx.x; t < total; t += (int64_t)gridDim.x * BLOCK) {
-        const int64_t u = t / Wout;
-        const int j = (int)(t - u * Wout);
-        const int64_t gb = (node_graph ? (int64_t)node_graph[u] : 0) * s_all;
-        uint64_t word = 0;
-        for (int b = 0; b < 64; ++b) {
-            const int i = j * 64 + b;
-            if (i >= s_all) break;
-            const int q = pos[gb + i];
-            const int grp = q / sg, p = q - grp * sg;
-            const uint64_t *row = sig + ((int64_t)grp * 2 + cur[grp]) * n * Wg + u * Wg;
-            word |= ((row[p >> 6] >> (p & 63)) & 1ull) << b;
+                                                       int sg, int k, const int32_t *cur, const int32_t *pos,
+                                                       const int32_t *node_graph, const int32_t *perm, uint64_t *out) {
+    __shared__ uint64_t s_w[RG_WORDS][RG_NODES];
+    __shared__ int32_t s_pos[64];   // of the output word's 64 bits: staged word << 6 | bit
+    const int tid = threadIdx.x;
+    const int total = k * Wg;   // words of a node over all groups
+    for (int64_t x0 = blockIdx.x * (int64_t)RG_NODES; x0 < n; x0 += (int64_t)gridDim.x * RG_NODES) {   // block-uniform
+        const int64_t x = x0 + tid;
+        const bool in = x < n;
+        const int64_t u = in ? (perm ? (int64_t)perm[x] : x) : 0;
+        const int64_t gb = node_graph && in ? (int64_t)node_graph[u] * s_all : 0;
+        for (int w0 = 0; w0 < total; w0 += RG_WORDS) {   // the groups' words, RG_WORDS at a time
+            const int nw = total - w0 < RG_WORDS ? total - w0 : RG_WORDS;
+            __syncthreads();
+            for (int q = 0; q < nw; ++q) {
+                const int grp = (w0 + q) / Wg, ww = (w0 + q) - grp * Wg;
+                s_w[q][tid] = in ? sig[(((int64_t)grp * 2 + cur[grp]) * n + u) * Wg + ww] : 0ull;
+            }
+            for (int j = 0; j < Wout; ++j) {
+                uint64_t word = 0;
+                if (!node_graph) {   // one table for the block
+                    __syncthreads();
+                    if (tid < 64) {
+                        const int i = j * 64 + tid;
+                        const int p = i < s_all ? pos[i] : -1;
+                        const int grp = p / sg, b = p - grp * sg, at = grp * Wg + (b >> 6) - w0;
+                        s_pos[tid] = p >= 0 && at >= 0 && at < nw ? (at << 6 | (b & 63)) : -1;
+                    }
+                    __syncthreads();
+#pragma unroll 8
+                    for (int b = 0; b < 64; ++b) {
+                        const int e = s_pos[b];   // block-uniform
+                        if (e >= 0) word |= ((s_w[e >> 6][tid] >> (e & 63)) & 1ull) << b;
+                    }
+                } else {
+                    for (int b = 0; b < 64; ++b) {
+                        const int i = j * 64 + b;
+                        if (i >= s_all) break;
+                        const int p = pos[gb + i], grp = p / sg, pb = p - grp * sg, at = grp * Wg + (pb >> 6) - w0;
+                        if (at >= 0 && at < nw) word |= ((s_w[at][tid] >> (pb & 63)) & 1ull) << b;
+                    }
+                }
+                if (in) {
+                    if (w0 == 0) out[x * Wout + j] = word;
+                    else if (word) out[x * Wout + j] |= word;
+                }
+            }
         }
-        out[t] = word;
     }
 }
 
@@ -612,11 +652,12 @@ hipError_t launch_seed_order(const GraphDev &g, const int32_t *seeds, const int3
     return hipGetLastError();
 }
 
-hipError_t launch_sig_regroup(const uint64_t *sig, int64_t n, int Wg, int Wout, int s_all, int sg, const int32_t *cur,
-                              const int32_t *pos, const int32_t *node_graph, uint64_t *out, hipStream_t st) {
+hipError_t launch_sig_regroup(const uint64_t *sig, int64_t n, int Wg, int Wout, int s_all, int sg, int k,
+                              const int32_t *cur, const int32_t *pos, const int32_t *node_graph, const int32_t *perm,
+                              uint64_t *out, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sig_regroup, dim3(fill_grid(n * Wout)), dim3(BLOCK), 0, st, sig, n, Wg, Wout, s_all, sg, cur,
-                       pos, node_graph, out);
+    hipLaunchKernelGGL(k_sig_regroup, dim3(fill_grid(n)), dim3(BLOCK), 0, st, sig, n, Wg, Wout, s_all, sg, k, cur, pos,
+                       node_graph, perm, out);
     return hipGetLastError();
 }
 
