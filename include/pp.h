@@ -105,7 +105,9 @@ typedef struct {
     int32_t rounds_per_sync;    /* rounds launched between host convergence checks (0: adaptive:
                                    8, then the rounds run so far, at most 64) */
     int32_t use_graph;          /* 1: replay the round batch as a captured hipGraph */
-    int32_t push_div;           /* heuristic: push while frontier arcs * push_div < arcs (0: 8) */
+    int32_t push_div;           /* heuristic: push while frontier arcs * push_div < arcs (0: 8);
+                                   on a large graph a pull instead while many nodes changed in
+                                   the pull before and it can stop lists early */
     uint64_t fuzz_seed;         /* PP_SCHED_FUZZ stream */
     int32_t time_kernels;       /* 1: HIP events around every pull launch (pp_get_kernel_times) */
     int32_t persistent;         /* 1: all rounds in one cooperative launch (grid barriers

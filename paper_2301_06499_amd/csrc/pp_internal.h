@@ -207,6 +207,13 @@ constexpr int EXIT_SHARE = 8;
 // 512 seeds: 3.9 -> 4.5 ms for its 16 groups; ER 10k: 192 -> 204 us; but
 // undirected R-MAT 17, 4M arcs: round 4 96 -> 45 us)
 constexpr int64_t EXIT_MIN_ARCS = (int64_t)1 << 20;
+// after a pull, the heuristic's push becomes another early-exit pull while one
+// node in EXIT_PULL_SHARE or more changed: the push would list all of them (two
+// rows read and a delta written each), the pull reads and writes each row once
+// (R-MAT 24 after the third pull, a quarter of the nodes changed: push 1.38 ms
+// with eight words and 0.82 ms with four, pull 0.46 and 0.26 ms; the round after
+// that, 0.4% changed, is a push either way; 16 and 64 measure the same)
+constexpr float EXIT_PULL_SHARE = 16;
 // blocks of the launch that take part (half of them with eight-word rows):
 // as many as are resident at once, since each block's start and sums cost more
 // than its share of a late round (R-MAT 24, eight words, the third pull: 1175

@@ -2571,7 +2571,11 @@ PP_DEV void phase_exit_decide(const GraphDev &g, const RunDev &R, int r) {
     const int64_t live = wave_sum((int)__popcll(gain));
     if (threadIdx.x == 0) {
         C->lst[r & 1] = ListCounts{0, 0};   // what an early-exit pull listed
-        C->exit_round = CTL(C->reached) * EXIT_SHARE >= g.open_nodes * live ? r + 1 : 0;
+        const bool exit = CTL(C->reached) * EXIT_SHARE >= g.open_nodes * live;
+        C->exit_round = exit ? r + 1 : 0;
+        // the heuristic's push would first list the pull's changed nodes: with
+        // many of them the early-exit pull is the cheaper round (EXIT_PULL_SHARE)
+        if (exit && R.sched == PP_SCHED_HEURISTIC && C->feat[0] * EXIT_PULL_SHARE >= 1.0f) C->mode = MODE_PULL;
     }
 }
 
