@@ -384,6 +384,8 @@ hipError_t launch_round(const GraphDev &g, const RunDev &r, hipStream_t st, hipE
 // The light rounds at the head of a batch (one graph, no round limit below the
 // log's capacity, rounds not timed one by one).
 hipError_t launch_light(const GraphDev &g, const RunDev &r, hipStream_t st);
+// Frontier entries and predecessor arcs that a light round of launch_light takes at most.
+void light_capacity(int W, int32_t *entries, int64_t *arcs);
 // Rounds up to max_round of every graph in one cooperative launch of `grid`
 // blocks split into clusters (device array), initialising graphs at round 0.
 hipError_t launch_batch_persistent(const GraphDev &g, const RunDev &r, const Cluster *clusters, int nclusters,

@@ -3132,6 +3132,11 @@ hipError_t launch_seed_init(const GraphDev &g, const RunDev &R, const int32_t *s
     }
 }
 
+void light_capacity(int W, int32_t *entries, int64_t *arcs) {
+    *entries = LightShape<1, LIGHT_THREADS>::LC / W;
+    *arcs = LightShape<1, LIGHT_THREADS>::H / W;
+}
+
 hipError_t launch_light(const GraphDev &g, const RunDev &R, hipStream_t st) {
     const dim3 grid(1, (unsigned)R.ngroups);
     switch (R.W) {
