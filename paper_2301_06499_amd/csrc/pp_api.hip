@@ -546,6 +546,7 @@ GraphDev graph_view(pp_graph g, const TileSet *ts, int W) {
     d.pull_grid = pp::pull_grid_for(d.ntiles, W);
     d.short_lists = ts && ts->short_lists ? 1 : 0;
     d.exit_ok = ts && g->G == 1 && !ts->short_lists && g->m >= pp::EXIT_MIN_ARCS ? 1 : 0;
+    d.symmetric = g->flags & PP_UNDIRECTED ? 1 : 0;
     d.open_nodes = ts ? g->n - ts->dead : 0;
     // rows of nodes without successors are skipped by the pull when there are
     // many (a quarter of the nodes or more) and the two signature buffers

@@ -184,6 +184,8 @@ struct GraphDev {
                                  // alone (many such nodes, rows beyond the caches)
     int32_t exit_ok;             // late pulls may stop lists early (one graph, not the short-list form)
     int64_t open_nodes;          // nodes with successors
+    int32_t symmetric;           // every node's predecessors are its successors (undirected input)
+    int32_t pad_graph;
 };
 
 // The early-exit pull (phase_pull_exit).

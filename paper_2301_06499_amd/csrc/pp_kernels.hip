@@ -265,6 +265,18 @@ template <int W> PP_DEV void seed_bits_keyed(const RunDev &R, int r, int gi, uin
     }
 }
 
+// The same where lane i holds the whole row of a node of graph gi (the whole
+// wave one graph).
+template <int W> PP_DEV void list_seed_bits(const RunDev &R, int r, int gi, const uint64_t (&d)[W]) {
+    const int64_t base = (int64_t)r * R.sstride + (int64_t)gi * R.sg;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        uint32_t one[1] = {0};
+        seed_ballot<1>(d[w], one);
+        if (one[0]) atomicAdd(&R.seed_counts[base + w * 64 + lane_id()], one[0]);
+    }
+}
+
 // Block-wide exclusive prefix sum of v in thread order, with the block total;
 // every thread of the block must call (scratch: BLOCK/64 ints of LDS).
 PP_DEV int block_scan(int v, int *scratch, int &total) {
@@ -871,11 +883,8 @@ template <int W> PP_DEV bool node_bit(uint64_t m, int j) {
     return (at >> 6) == j && ((m >> (at & 63)) & WordMask<W>::row) != 0;
 }
 
-// SHORT: every tile of the graph takes the one-lane-per-node gather (rows of
-// one or two words, no high-degree chunks): the general gather is not
-// compiled in, which leaves the kernel fewer registers and more waves.
 // DEAD: the rows of nodes without successors are left alone (see below).
-template <int W, int KK = 0, bool SHORT = false, bool DEAD = false>
+template <int W, int KK = 0, bool DEAD = false>
 PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
     Ctrl *C = R.ctrl;
     using PS = PullShape<W, KK>;
@@ -966,7 +975,7 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
         // (neighbouring rows on a lattice: few cache lines per load)
         constexpr int NPL = PULL_NPL;
         int dmax = 0;
-        if constexpr (W <= 2 && !SHORT) {
+        if constexpr (W <= 2) {
             if (!hub) {
                 int d = ln < nn ? rp_l[ln + 1] - rp_l[ln] : 0;
 #pragma unroll
@@ -974,7 +983,7 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
                 dmax = d;
             }
         }
-        if (SHORT || (W <= 2 && !hub && dmax <= NPL)) {
+        if (W <= 2 && !hub && dmax <= NPL) {
             const int b0 = ln < nn ? rp_l[ln] : 0;
             const int d = ln < nn ? rp_l[ln + 1] - b0 : 0;
             uint64_t rows[NPL][W];
@@ -993,7 +1002,7 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
                     acc_l[ln * W + w] = a;
                 }
             }
-        } else if constexpr (!SHORT) {
+        } else {
         // gather: a group of L lanes shares arcs [a, a + KG); each lane loads
         // and ORs its P-word slice of every source row (one 16-byte load per
         // lane, so the group's loads of one row fall in one cache line and
@@ -1381,6 +1390,122 @@ PP_DEV void phase_pull_rest(const GraphDev &g, const RunDev &R, int bid, int nb)
                 atomicOr((unsigned long long *)&R.acc[(int64_t)u * W + sub * P + k], (unsigned long long)add);
         }
     }
+}
+
+// The pull of a graph whose lists are all short (at most PULL_NPL successors,
+// rows of one or two words): lane i of a wave holds the tile's node i, its row
+// and its gathered successors in registers, so load j of the wave takes the j-th
+// successor of 64 consecutive nodes (neighbouring rows on a lattice), and no row
+// goes through LDS, only the tile's column ids.
+// What bounds it now is the bytes: 1.61 GB counted per launch on the 4096^2
+// lattice, s = 128 (305 us before, through LDS rows with two waits after the
+// gather; 218 us in this form, whose one chain per tile is the gather: the
+// changed nodes' predecessor counts come from the offsets at hand where the
+// graph is symmetric).  At 1024 blocks; 768, 1280 and 2048: 1%, 5% and 16% more
+// per propagation; six waves per SIMD (8 registers spilled) 4% more; block ids
+// permuted so that each XCD takes neighbouring tiles: the same.
+template <int W>
+PP_DEV void phase_pull_lists(const GraphDev &g, const RunDev &R, int bid, int nb) {
+    Ctrl *C = R.ctrl;
+    constexpr int K = PullShape<W>::K, EDGES = PullShape<W>::EDGES, NODES = PullShape<W>::NODES;
+    constexpr int WAVES = BLOCK / 64;
+    constexpr int NPL = PULL_NPL;
+    __shared__ int32_t s_col[WAVES][EDGES];
+    __shared__ unsigned long long s_red[BLOCK / 64];
+    const int r = CTL(C->round);
+    const int cur = CTL(C->cur);
+    const uint64_t *__restrict__ sig = sel(R.sig, cur);
+    uint64_t *__restrict__ nxt = sel(R.sig, cur ^ 1);
+    const int ln = lane_id(), wv = threadIdx.x >> 6;
+    int32_t *col_l = s_col[wv];
+    const bool per_seed = R.seed_counts != nullptr;
+    uint32_t pop = 0, nodes = 0;
+    int64_t parcs = 0, pulled = 0;
+    uint32_t sc[W];   // lane b: nodes that gained bit b of word w
+#pragma unroll
+    for (int w = 0; w < W; ++w) sc[w] = 0;
+    const int64_t nw = (int64_t)nb * WAVES;
+    int64_t t = (int64_t)bid * WAVES + wv;
+    Tile T = t < g.ntiles ? g.tiles[t] : Tile{0, 0, 0, 0, -1, 0};
+    int32_t cv[K];
+    int32_t rv0 = 0, rv1 = 0;
+    stage_tile<K, NODES>(g, T, ln, cv, rv0, rv1);
+    for (; t < g.ntiles; t += nw) {   // wave-uniform
+        const int64_t tn = t + nw;
+        const Tile Tn = tn < g.ntiles ? g.tiles[tn] : T;
+        const int nn = T.u1 - T.u0, ne = (int)(T.e1 - T.e0);
+        const int64_t u = (int64_t)T.u0 + ln;
+        const bool in = ln < nn;
+        const bool skip = R.G > 1 && R.gconv[T.graph];   // converged: its rows only go to the other buffer
+        const int b = rv0;
+        int e = __shfl_down(rv0, 1);
+        if (ln == 63) e = ne;   // (a full tile ends with its last arc)
+        const int d = in && !skip ? e - b : 0;
+        uint64_t own[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) own[w] = 0;
+        if (in) load_row<W>(sig + u * W, own);
+#pragma unroll
+        for (int j = 0; j < K; ++j) col_l[ln + j * 64] = cv[j];
+        wave_lds_fence();
+        uint64_t rows[NPL][W];
+#pragma unroll
+        for (int j = 0; j < NPL; ++j) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) rows[j][w] = 0;
+            if (j < d) load_row<W>(sig + (int64_t)col_l[b + j] * W, rows[j]);
+        }
+        if (tn < g.ntiles) stage_tile<K, NODES>(g, Tn, ln, cv, rv0, rv1);
+        uint64_t nb2[W];
+        bool changed = false;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            uint64_t a = 0;
+#pragma unroll
+            for (int j = 0; j < NPL; ++j) a |= rows[j][w];
+            nb2[w] = a & ~own[w];
+            own[w] |= a;
+            changed |= nb2[w] != 0;
+        }
+        if (in) store_row<W>(nxt + u * W, own);
+        if (ln == 0 && !skip) pulled += ne;
+        uint32_t c = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) c += (uint32_t)__popcll(nb2[w]);
+        if (changed) {
+            ++nodes;
+            parcs += g.symmetric ? d : (int)(g.trp[u + 1] - g.trp[u]);
+            R.stamp[u] = r;   // changed in this round: listed by a push that follows
+        }
+        if (R.G == 1) {
+            pop += c;
+            if (per_seed) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    uint32_t one[1] = {sc[w]};
+                    seed_ballot<1>(nb2[w], one);
+                    sc[w] = one[0];
+                }
+            }
+        } else {
+            const uint32_t tt = wave_sum(c);
+            if (ln == 0 && tt) atomicAdd((unsigned long long *)&R.counts[(int64_t)r * R.cstride + T.graph], (unsigned long long)tt);
+            if (per_seed) list_seed_bits<W>(R, r, T.graph, nb2);
+        }
+        wave_lds_fence();
+        T = Tn;
+    }
+    const unsigned long long tp = block_sum<unsigned long long>(pop, s_red);
+    const unsigned long long tn = block_sum<unsigned long long>(nodes, s_red);
+    const unsigned long long ta = block_sum<unsigned long long>((unsigned long long)parcs, s_red);
+    const unsigned long long tq = block_sum<unsigned long long>((unsigned long long)pulled, s_red);
+    if (threadIdx.x == 0) {
+        R.blk_cnt[bid] = (int64_t)tp;
+        R.blk_nodes[bid] = (int64_t)tn;
+        R.blk_arcs[bid] = (int64_t)ta;
+        R.blk_pulled[bid] = (int64_t)tq;
+    }
+    if (per_seed && R.G == 1) seed_flush<W>(R, r, sc);
 }
 
 // High-degree nodes of a pull round: the chunks left their ORed rows in the
@@ -2606,7 +2731,7 @@ k_pull(GraphDev g, RunDev R0) {
         if (exits(g, C, C->round)) {
             const int nb = exit_blocks(gridDim.x, W);
             if (blockIdx.x < nb) phase_pull_exit<W>(g, R, blockIdx.x, nb);
-        } else phase_pull<W, KK, false, DEAD>(g, R, blockIdx.x, gridDim.x);
+        } else phase_pull<W, KK, DEAD>(g, R, blockIdx.x, gridDim.x);
     } else if (C->prev_mode == MODE_PULL && blockIdx.x < FRONTIER_BLOCKS) {
         const int nb = gridDim.x < FRONTIER_BLOCKS ? (int)gridDim.x : FRONTIER_BLOCKS;
         phase_frontier<W, 1024>(g, R, blockIdx.x, nb);
@@ -2625,7 +2750,7 @@ k_pull_short(GraphDev g, RunDev R0) {
         if (r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
     }
     if (C->mode == MODE_PULL) {
-        phase_pull<W, 0, true>(g, R, blockIdx.x, gridDim.x);
+        phase_pull_lists<W>(g, R, blockIdx.x, gridDim.x);
     } else if (C->prev_mode == MODE_PULL && blockIdx.x < FRONTIER_BLOCKS) {
         const int nb = gridDim.x < FRONTIER_BLOCKS ? (int)gridDim.x : FRONTIER_BLOCKS;
         phase_frontier<W, 1024>(g, R, blockIdx.x, nb);
