@@ -137,7 +137,7 @@ struct pp_graph_s {
     int32_t *perm_d = nullptr;      // the same on the device
     std::vector<uint64_t> pred_bits;  // bit u (stored id): node u has a predecessor
     int32_t *seq_heavy = nullptr;   // PROPAGATE-S: nodes with more than SEQ_LIGHT successors
-    int64_t nseq_heavy = 0;
+    int64_t nseq_heavy = 0, nseq_giant = 0;   // (the first nseq_giant of them: more than SEQ_GIANT)
 };
 
 struct pp_run_s {
@@ -790,6 +790,9 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
         std::vector<int32_t> hv;
         for (int64_t u = 0; u < n; ++u)
             if (rp[(size_t)u + 1] - rp[(size_t)u] > pp::SEQ_LIGHT) hv.push_back((int32_t)u);
+        g->nseq_giant = std::stable_partition(hv.begin(), hv.end(), [&](int32_t u) {
+            return rp[(size_t)u + 1] - rp[(size_t)u] > pp::SEQ_GIANT;
+        }) - hv.begin();
         if ((rc = dev_alloc(&g->seq_heavy, (int64_t)hv.size()))) {
             free_graph(g);
             return rc;
@@ -2495,7 +2498,7 @@ int propagate_s_rows(pp_graph g, const int32_t *seeds, int32_t s, void *region, 
         while (running && last + 1 < cap_rounds && e == hipSuccess) {
             const int upto = std::min(last + 8, cap_rounds - 1);
             for (int r = last + 1; r <= upto && e == hipSuccess; ++r)
-                e = pp::launch_seq_rows(gv, S, g->seq_heavy, g->nseq_heavy, r, st);
+                e = pp::launch_seq_rows(gv, S, g->seq_heavy, g->nseq_heavy, g->nseq_giant, r, st);
             last = upto;
             if (e == hipSuccess)
                 e = hipMemcpyAsync(hc.data() + read, S.sum_cnt + read, sizeof(int64_t) * (size_t)(last + 1 - read),

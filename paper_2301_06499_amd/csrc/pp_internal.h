@@ -343,14 +343,19 @@ struct SeqRows {
     int32_t row_bytes, pad;
 };
 hipError_t launch_seq_rows_seeds(const SeqRows &S, const int32_t *seeds, int kk, hipStream_t st);
-hipError_t launch_seq_rows(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int r,
-                           hipStream_t st);
+// heavy: the ngiant nodes with more than SEQ_GIANT successors first.
+hipError_t launch_seq_rows(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int64_t ngiant,
+                           int r, hipStream_t st);
 hipError_t launch_seq_seeds(const SeqDev &S, const int32_t *seeds, int kk, hipStream_t st);
 // The current device's address of the fixed PP_NOALLOC_BYTES region that
 // pp_propagate_s_noalloc carves its buffers from (looked up once per device).
 int noalloc_region(void **out);
 // Nodes with more successors than this go to the wave-per-node launch.
 constexpr int SEQ_LIGHT = 32;
+// and, on node-major rows, nodes with more than this many to a block each
+// (R-MAT 20, 256 seeds, per call: 1.23 ms without, 949 us from 512 on, 917 from
+// 1024, 871 from 4096, 933 from 16384)
+constexpr int SEQ_GIANT = 4096;
 // Pass r (short lists, then heavy[0..nheavy)) and its per-seed end.
 hipError_t launch_seq_pass(const GraphDev &g, const SeqDev &S, const int32_t *heavy, int64_t nheavy, int r,
                            int blocks_per_seed, int heavy_blocks_per_seed, hipStream_t st);

@@ -268,25 +268,125 @@ template <typename T> PS_DEV T from_lane(T v, int lane_) {
 
 }  // namespace
 
+// Node u's list, walked by NWV waves (one, or the whole block) in steps of
+// NWV x 64 / L x SEQ_STEP consecutive arcs: each group of L lanes (16 bytes of a
+// row per lane) gathers SEQ_STEP of them, an exclusive prefix OR over the groups
+// (and, through LDS, over the waves) gives every group the bits still pending
+// at its first arc, and a step whose rows are all zero skips it.  The new row
+// goes to nxt.  Bound by the chain of steps of the longest lists, which is why
+// they take a block (R-MAT 20, 256 seeds, passes 1 and 2, which walk every list to
+// its end: 377 and 324 us with a wave each, 150 and 151 us).
+constexpr int SEQ_STEP = 4;
+template <typename T, int W, int NWV>
+PS_DEV void walk_list(const GraphDev &g, const T *cur, T *nxt, int32_t u, const T *rn, T *gain, int64_t &found,
+                      int64_t &exam) {
+    constexpr int L = W >= 2 ? W / 2 : 1, P = W / L, NG = 64 / L, ST = SEQ_STEP;
+    __shared__ T s_or[2][NWV][W];
+    const int ln = lane(), sub = ln % L, grp = ln / L, wv = NWV > 1 ? threadIdx.x >> 6 : 0;
+    const int64_t mine = ((int64_t)wv * NG + grp) * ST;   // the group's first arc of a step
+    int64_t a = g.rp[u];
+    const int64_t e = g.rp[u + 1];
+    T row[P], pend[P];
+    load_slice<T, P>(cur + (int64_t)u * W + sub * P, row);
+#pragma unroll
+    for (int k = 0; k < P; ++k) pend[k] = rn[k] & (T)~row[k];
+    int32_t v[ST];
+#pragma unroll
+    for (int q = 0; q < ST; ++q) v[q] = a + mine + q < e ? g.col[a + mine + q] : -1;
+    int par = 0;
+    while (a < e && __ballot(any_bit<T, P>(pend))) {   // the same in every wave
+        T rows[ST][P];
+#pragma unroll
+        for (int q = 0; q < ST; ++q) {
+            if (v[q] >= 0) {
+                load_slice<T, P>(cur + (int64_t)v[q] * W + sub * P, rows[q]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < P; ++k) rows[q][k] = 0;
+            }
+        }
+        const int64_t left = e - (a + mine);   // arcs from the group's first on
+        a += NWV * NG * ST;
+#pragma unroll
+        for (int q = 0; q < ST; ++q) v[q] = a + mine + q < e ? g.col[a + mine + q] : -1;
+        T o[P], p[P], all[P];   // the groups' ORs up to this one; bits pending here; the step's OR
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            o[k] = 0;
+#pragma unroll
+            for (int q = 0; q < ST; ++q) o[k] |= rows[q][k];
+            p[k] = pend[k];
+            all[k] = 0;
+        }
+        if (__ballot(any_bit<T, P>(o))) {   // wave-uniform
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+#pragma unroll
+                for (int d = L; d < 64; d <<= 1) {   // inclusive prefix OR over the groups
+                    const T t = from_lane<T>(o[k], ln - d < 0 ? ln : ln - d);
+                    o[k] |= t;
+                }
+                const T before = from_lane<T>(o[k], ln < L ? ln : ln - L);
+                p[k] &= (T)~(ln < L ? (T)0 : before);
+                all[k] = from_lane<T>(o[k], 64 - L + sub);
+            }
+        }
+        if constexpr (NWV > 1) {   // the waves before this one, and all of them
+            if (grp == 0) store_slice<T, P>(&s_or[par][wv][sub * P], all);
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < P; ++k) all[k] = 0;
+#pragma unroll
+            for (int w = 0; w < NWV; ++w) {
+                T x[P];
+                load_slice<T, P>(&s_or[par][w][sub * P], x);
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    if (w < wv) p[k] &= (T)~x[k];
+                    all[k] |= x[k];
+                }
+            }
+            par ^= 1;
+        }
+#pragma unroll
+        for (int k = 0; k < P; ++k) pend[k] &= (T)~all[k];
+#pragma unroll
+        for (int q = 0; q < ST; ++q) {
+            if (q < left) exam += bits<T, P>(p);
+#pragma unroll
+            for (int k = 0; k < P; ++k) p[k] &= (T)~rows[q][k];
+        }
+    }
+    if (grp == 0 && wv == 0) {
+        T nb[P];
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            nb[k] = rn[k] & (T)~row[k] & (T)~pend[k];
+            row[k] |= nb[k];
+            gain[k] |= nb[k];
+        }
+        found += bits<T, P>(nb);
+        store_slice<T, P>(nxt + (int64_t)u * W + sub * P, row);
+    }
+    if constexpr (NWV > 1) __syncthreads();   // the LDS words before the next node's
+}
+
 // Pass r of every seed in flight on rows of W words of type T (bit i: seed i).
 // A node's pending bits are the running seeds that have not reached it; its
 // list is walked in order, each arc adds one examined arc per pending bit and
 // clears the bits of its successor's row, and the walk ends when none is left:
 // each seed's early break at its own first hit, counted as if it walked alone.
-// The first heavy_blocks blocks take the nodes with more than SEQ_LIGHT
-// successors, one per wave: its groups of L lanes (16 bytes of a row per lane)
-// gather SEQ_STEP consecutive arcs each, and an exclusive prefix OR over the
-// groups gives every group the bits still pending at its first arc.  The other
-// blocks take the rest, one node per group.  Every node's row goes to the next
-// buffer.
+// The first giant_blocks blocks take the nodes with more than SEQ_GIANT
+// successors, one per block, the next heavy_blocks those with more than
+// SEQ_LIGHT, one per wave (walk_list); the other blocks take the rest, one node
+// per group of L lanes.  Every node's row goes to the next buffer.
 // Bound by the gathers of a dense round (one row per arc serves every seed),
 // like the pull of PROPAGATE-P; the seed-major form gathers a word per arc and
 // seed.  R-MAT 20, 256 seeds, per call: 22.8 ms seed-major (two launches of
-// passes, 22.1 ms in them), 1.22 ms here (1.14 ms in the passes).
-constexpr int SEQ_STEP = 4;
+// passes, 22.1 ms in them), 0.87 ms here (0.82 ms in the passes).
 template <typename T, int W>
-__global__ void __launch_bounds__(BLOCK) k_seq_rows(GraphDev g, SeqRows S, const int32_t *heavy, int64_t nheavy, int r,
-                                                   int heavy_blocks) {
+__global__ void __launch_bounds__(BLOCK) k_seq_rows(GraphDev g, SeqRows S, const int32_t *heavy, int64_t nheavy,
+                                                   int64_t ngiant, int r, int giant_blocks, int heavy_blocks) {
     constexpr int L = W >= 2 ? W / 2 : 1;   // lanes per row
     constexpr int P = W / L;                // words per lane
     constexpr int NG = 64 / L;              // groups per wave
@@ -309,71 +409,17 @@ __global__ void __launch_bounds__(BLOCK) k_seq_rows(GraphDev g, SeqRows S, const
 #pragma unroll
     for (int k = 0; k < P; ++k) gain[k] = 0;
 
-    if ((int)blockIdx.x < heavy_blocks) {
+    if ((int)blockIdx.x < giant_blocks) {
+        for (int64_t h = blockIdx.x; h < ngiant; h += giant_blocks)   // block-uniform
+            walk_list<T, W, BLOCK / 64>(g, cur, nxt, heavy[h], rn, gain, found, exam);
+    } else if ((int)blockIdx.x < giant_blocks + heavy_blocks) {
         const int64_t nw = (int64_t)heavy_blocks * (BLOCK / 64);
-        for (int64_t h = (int64_t)blockIdx.x * (BLOCK / 64) + wv; h < nheavy; h += nw) {   // wave-uniform
-            const int32_t u = heavy[h];
-            int64_t a = g.rp[u];
-            const int64_t e = g.rp[u + 1];
-            T row[P], pend[P];
-            load_slice<T, P>(cur + (int64_t)u * W + sub * P, row);
-#pragma unroll
-            for (int k = 0; k < P; ++k) pend[k] = rn[k] & (T)~row[k];
-            int32_t v[ST];
-#pragma unroll
-            for (int q = 0; q < ST; ++q) v[q] = a + grp * ST + q < e ? g.col[a + grp * ST + q] : -1;
-            while (a < e && __ballot(any_bit<T, P>(pend))) {   // wave-uniform
-                T rows[ST][P];
-#pragma unroll
-                for (int q = 0; q < ST; ++q) {
-                    if (v[q] >= 0) {
-                        load_slice<T, P>(cur + (int64_t)v[q] * W + sub * P, rows[q]);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < P; ++k) rows[q][k] = 0;
-                    }
-                }
-                const int64_t left = e - (a + grp * ST);   // arcs from the group's first on
-                a += NG * ST;
-#pragma unroll
-                for (int q = 0; q < ST; ++q) v[q] = a + grp * ST + q < e ? g.col[a + grp * ST + q] : -1;
-                T p[P];
-#pragma unroll
-                for (int k = 0; k < P; ++k) {
-                    T o = 0;
-#pragma unroll
-                    for (int q = 0; q < ST; ++q) o |= rows[q][k];
-#pragma unroll
-                    for (int d = L; d < 64; d <<= 1) {   // inclusive prefix OR over the groups
-                        const T t = from_lane<T>(o, ln - d < 0 ? ln : ln - d);
-                        o |= t;
-                    }
-                    const T before = from_lane<T>(o, ln < L ? ln : ln - L);
-                    p[k] = pend[k] & (T)~(ln < L ? (T)0 : before);
-                    pend[k] &= (T)~from_lane<T>(o, 64 - L + sub);
-                }
-#pragma unroll
-                for (int q = 0; q < ST; ++q) {
-                    if (q < left) exam += bits<T, P>(p);
-#pragma unroll
-                    for (int k = 0; k < P; ++k) p[k] &= (T)~rows[q][k];
-                }
-            }
-            if (grp == 0) {
-                T nb[P];
-#pragma unroll
-                for (int k = 0; k < P; ++k) {
-                    nb[k] = rn[k] & (T)~row[k] & (T)~pend[k];
-                    row[k] |= nb[k];
-                    gain[k] |= nb[k];
-                }
-                found += bits<T, P>(nb);
-                store_slice<T, P>(nxt + (int64_t)u * W + sub * P, row);
-            }
-        }
+        for (int64_t h = ngiant + (int64_t)(blockIdx.x - giant_blocks) * (BLOCK / 64) + wv; h < nheavy; h += nw)   // wave-uniform
+            walk_list<T, W, 1>(g, cur, nxt, heavy[h], rn, gain, found, exam);
     } else {
-        const int64_t nw = (int64_t)(gridDim.x - heavy_blocks) * (BLOCK / 64);
-        const int64_t first = (int64_t)(blockIdx.x - heavy_blocks) * (BLOCK / 64) + wv;
+        const int before = giant_blocks + heavy_blocks;
+        const int64_t nw = (int64_t)(gridDim.x - before) * (BLOCK / 64);
+        const int64_t first = (int64_t)(blockIdx.x - before) * (BLOCK / 64) + wv;
         for (int64_t u0 = first * NG; u0 < g.n; u0 += nw * NG) {   // wave-uniform
             const int64_t u = u0 + grp;
             int64_t a = 0;
@@ -478,25 +524,26 @@ hipError_t launch_seq_rows_seeds(const SeqRows &S, const int32_t *seeds, int kk,
 }
 
 template <typename T, int W>
-static hipError_t seq_rows_impl(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int r,
-                                hipStream_t st) {
+static hipError_t seq_rows_impl(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy,
+                                int64_t ngiant, int r, hipStream_t st) {
     constexpr int NG = 64 / (W >= 2 ? W / 2 : 1);
-    const int64_t hb = (nheavy + BLOCK / 64 - 1) / (BLOCK / 64), lb = (g.n + NG * (BLOCK / 64) - 1) / (NG * (BLOCK / 64));
+    const int64_t hb = (nheavy - ngiant + BLOCK / 64 - 1) / (BLOCK / 64), lb = (g.n + NG * (BLOCK / 64) - 1) / (NG * (BLOCK / 64));
     const int nh = (int)(hb < SEQ_BLOCKS ? hb : SEQ_BLOCKS), nl = (int)(lb < SEQ_BLOCKS ? lb : SEQ_BLOCKS);
-    hipLaunchKernelGGL((k_seq_rows<T, W>), dim3(nh + nl), dim3(BLOCK), 0, st, g, S, heavy, nheavy, r, nh);
+    const int ng = (int)(ngiant < SEQ_BLOCKS ? ngiant : SEQ_BLOCKS);
+    hipLaunchKernelGGL((k_seq_rows<T, W>), dim3(ng + nh + nl), dim3(BLOCK), 0, st, g, S, heavy, nheavy, ngiant, r, ng, nh);
     return hipGetLastError();
 }
 
-hipError_t launch_seq_rows(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int r,
-                           hipStream_t st) {
+hipError_t launch_seq_rows(const GraphDev &g, const SeqRows &S, const int32_t *heavy, int64_t nheavy, int64_t ngiant,
+                           int r, hipStream_t st) {
     switch (S.row_bytes) {
-        case 1: return seq_rows_impl<uint8_t, 1>(g, S, heavy, nheavy, r, st);
-        case 2: return seq_rows_impl<uint16_t, 1>(g, S, heavy, nheavy, r, st);
-        case 4: return seq_rows_impl<uint32_t, 1>(g, S, heavy, nheavy, r, st);
-        case 8: return seq_rows_impl<uint64_t, 1>(g, S, heavy, nheavy, r, st);
-        case 16: return seq_rows_impl<uint64_t, 2>(g, S, heavy, nheavy, r, st);
-        case 32: return seq_rows_impl<uint64_t, 4>(g, S, heavy, nheavy, r, st);
-        case 64: return seq_rows_impl<uint64_t, 8>(g, S, heavy, nheavy, r, st);
+        case 1: return seq_rows_impl<uint8_t, 1>(g, S, heavy, nheavy, ngiant, r, st);
+        case 2: return seq_rows_impl<uint16_t, 1>(g, S, heavy, nheavy, ngiant, r, st);
+        case 4: return seq_rows_impl<uint32_t, 1>(g, S, heavy, nheavy, ngiant, r, st);
+        case 8: return seq_rows_impl<uint64_t, 1>(g, S, heavy, nheavy, ngiant, r, st);
+        case 16: return seq_rows_impl<uint64_t, 2>(g, S, heavy, nheavy, ngiant, r, st);
+        case 32: return seq_rows_impl<uint64_t, 4>(g, S, heavy, nheavy, ngiant, r, st);
+        case 64: return seq_rows_impl<uint64_t, 8>(g, S, heavy, nheavy, ngiant, r, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -11,10 +11,11 @@ from paper_2301_06499_amd import pp
 
 pytestmark = pytest.mark.gpu
 
-# lists far longer than a wave's step; long passes; no arcs at all.  Node counts
+# lists far longer than a wave's step, and one that a whole block walks; long
+# passes; no arcs at all.  Node counts
 # that are no multiple of 4 or 64, and seeds at 12 nodes only: the oracle runs
 # once per node, and its figures add up over the seeds.
-GRAPHS = {"rmat": (gen.rmat(9, 90, 3), 3), "path": (gen.path_graph(131), 0),
+GRAPHS = {"rmat": (gen.rmat(9, 90, 3), 3), "path": (gen.path_graph(131), 0), "star": (gen.star_graph(9003), 2),
           "empty": (gen.Graph(5, np.zeros(0, np.int32), np.zeros(0, np.int32), False), 0)}
 
 
