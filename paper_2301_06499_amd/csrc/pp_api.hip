@@ -683,7 +683,8 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
         }
         pp::DevRows rows, trows;
         if (tr) std::swap(a, b);
-        rc = pp::device_build(n, m, a, b, und, order, rows, trows, perm, st);
+        rc = pp::device_build(n, m, a, b, und, order, G == 1 && !(flags & (PP_KEEP_ORDER | PP_HUBS_ONLY)), rows, trows,
+                              perm, st);
         drop_input();   // device_build has synchronised the stream
         g->rp = rows.rp;
         g->col = rows.col;
