@@ -586,6 +586,12 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
     const bool tr = flags & PP_TRANSPOSE;
     const bool on_device = (flags & PP_BUILD_ON_DEVICE) || (!(flags & PP_BUILD_ON_HOST) && m >= PP_DEVICE_BUILD_MIN);
     hipStream_t st = (hipStream_t)stream;
+    // a small build the library put on the device goes to the host threads when
+    // the device has no memory for its keys
+    auto retry = [&](int code) -> int {
+        if (code != PP_ENOMEM || (flags & PP_BUILD_ON_DEVICE) || m >= (int64_t)1 << 20) return code;
+        return pp_csr_build(n, m, src, dst, flags | PP_BUILD_ON_HOST, node_offsets, num_graphs, stream, out);
+    };
     std::vector<int32_t> ng;
     if (G > 1) {
         ng.resize((size_t)n);
@@ -652,8 +658,9 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
         if (!(flags & PP_INPUT_ON_DEVICE) && m > 0) {
             if ((rc = dev_alloc(&da, m)) || (rc = dev_alloc(&db, m))) {
                 drop_input();
+                (void)hipStreamSynchronize(st);   // the uploads above read host memory
                 free_graph(g);
-                return rc;
+                return retry(rc);
             }
             e = hipMemcpyAsync(da, src, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, st);
             if (e == hipSuccess) e = hipMemcpyAsync(db, dst, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, st);
@@ -670,7 +677,7 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
         if ((flags & PP_INPUT_ON_DEVICE) && (rc = pp::device_check_arcs(a, b, m, n, g->node_graph, &bad, st))) {
             drop_input();
             free_graph(g);
-            return rc;
+            return retry(rc);
         }
         if (bad >= 0) {
             int32_t ends[2] = {0, 0};
@@ -692,8 +699,9 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
         g->tcol = trows.col;
         g->m = rows.m;
         if (rc) {
+            (void)hipStreamSynchronize(st);
             free_graph(g);
-            return rc;
+            return retry(rc);
         }
         // host copies of the offsets (tiles, the long-list table, predecessor bits)
         try {

@@ -21,7 +21,7 @@ LIB_PATH = os.path.join(_PKG, "libpp.so")
 PP_OK, PP_EINVAL, PP_ERANGE, PP_ENOMEM, PP_EDEVICE, PP_ENOTCONV, PP_ESTATE = 0, -1, -2, -3, -4, -5, -6
 PP_UNDIRECTED, PP_INPUT_ON_DEVICE, PP_TRANSPOSE, PP_KEEP_ORDER = 1, 2, 4, 8
 PP_BUILD_ON_HOST, PP_BUILD_ON_DEVICE, PP_HUBS_ONLY = 16, 32, 64
-DEVICE_BUILD_MIN = 1 << 20
+DEVICE_BUILD_MIN = 1
 PP_SCHED_HEURISTIC, PP_SCHED_PULL, PP_SCHED_PUSH, PP_SCHED_FUZZ, PP_SCHED_MLP, PP_SCHED_PLAN = 0, 1, 2, 3, 4, 5
 PP_GROUPS_BY_REACH, PP_ORDER_BY_REACH = -1, 1
 MODE_PULL, MODE_PUSH, MODE_INIT, MODE_SPULL, MODE_PUSH_FLAT = 0, 1, 2, 3, 4   # entries of the per-round mode log
