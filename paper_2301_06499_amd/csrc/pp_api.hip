@@ -1995,24 +1995,16 @@ extern "C" int pp_get_node_stats(pp_run r, int32_t *reached, int64_t *dist_sum) 
         dev_free(dr);
         return rc;
     }
-    std::vector<int32_t> hr((size_t)n);
-    std::vector<int64_t> hd((size_t)n);
     // the per-round engine (node_stats excludes the clustered one) keeps Sig in one buffer
-    hipError_t e = pp::launch_node_stats(r->dev.sig[r->host_ctrl.cur & 1], r->dev.node_acc, n, r->W, K, dr, dd,
-                                         r->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(hr.data(), dr, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, r->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(hd.data(), dd, sizeof(int64_t) * (size_t)n, hipMemcpyDeviceToHost, r->stream);
+    hipError_t e = pp::launch_node_stats(r->dev.sig[r->host_ctrl.cur & 1], r->dev.node_acc, r->g->perm_d, n, r->W, K,
+                                         dr, dd, r->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(reached, dr, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, r->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(dist_sum, dd, sizeof(int64_t) * (size_t)n, hipMemcpyDeviceToHost, r->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(r->stream);
     if (e != hipSuccess) (void)hipStreamSynchronize(r->stream);
     dev_free(dr);
     dev_free(dd);
     if (e != hipSuccess) return fail(PP_EDEVICE, "node statistics: %s", hipGetErrorString(e));
-    const std::vector<int32_t> &perm = r->g->perm;
-    for (int64_t u = 0; u < n; ++u) {
-        const size_t x = perm.empty() ? (size_t)u : (size_t)perm[(size_t)u];
-        reached[u] = hr[x];
-        dist_sum[u] = hd[x];
-    }
     return PP_OK;
 }
 

@@ -360,10 +360,11 @@ constexpr int SEQ_GIANT = 4096;
 hipError_t launch_seq_pass(const GraphDev &g, const SeqDev &S, const int32_t *heavy, int64_t nheavy, int r,
                            int blocks_per_seed, int heavy_blocks_per_seed, hipStream_t st);
 
-// Per-node statistics: reached[u] = popcount of u's row of sig, dist_sum[u]
-// = K reached[u] - acc[u] (K states accumulated).
-hipError_t launch_node_stats(const uint64_t *sig, const int64_t *acc, int64_t n, int W, int64_t K, int32_t *reached,
-                             int64_t *dist_sum, hipStream_t st);
+// Per-node statistics of input node x, stored at u = perm[x] (perm NULL: x):
+// reached[x] = popcount of u's row of sig, dist_sum[x] = K reached[x] - acc[u]
+// (K states accumulated).
+hipError_t launch_node_stats(const uint64_t *sig, const int64_t *acc, const int32_t *perm, int64_t n, int W, int64_t K,
+                             int32_t *reached, int64_t *dist_sum, hipStream_t st);
 
 hipError_t launch_stage(const void *ctrl, int64_t ctrl_bytes, const int32_t *D, int64_t nD, const int64_t *rows,
                         int64_t nrows, void *h_ctrl, int32_t *h_D, int64_t *h_rows, hipStream_t st);

@@ -2902,19 +2902,21 @@ template <int W> __global__ void __launch_bounds__(BLOCK) k_node_acc(GraphDev g,
     }
 }
 
-__global__ void __launch_bounds__(BLOCK) k_node_stats(const uint64_t *sig, const int64_t *acc, int64_t n, int W,
-                                                      int64_t K, int32_t *reached, int64_t *dist_sum) {
-    for (int64_t u = blockIdx.x * (int64_t)BLOCK + threadIdx.x; u < n; u += (int64_t)gridDim.x * BLOCK) {
+// By input node x, stored at perm[x] (perm NULL: x).
+__global__ void __launch_bounds__(BLOCK) k_node_stats(const uint64_t *sig, const int64_t *acc, const int32_t *perm,
+                                                      int64_t n, int W, int64_t K, int32_t *reached, int64_t *dist_sum) {
+    for (int64_t x = blockIdx.x * (int64_t)BLOCK + threadIdx.x; x < n; x += (int64_t)gridDim.x * BLOCK) {
+        const int64_t u = perm ? perm[x] : x;
         int c = 0;
         for (int w = 0; w < W; ++w) c += __popcll(sig[u * W + w]);
-        reached[u] = c;
-        dist_sum[u] = K * (int64_t)c - acc[u];
+        reached[x] = c;
+        dist_sum[x] = K * (int64_t)c - acc[u];
     }
 }
 
-hipError_t launch_node_stats(const uint64_t *sig, const int64_t *acc, int64_t n, int W, int64_t K, int32_t *reached,
-                             int64_t *dist_sum, hipStream_t st) {
-    hipLaunchKernelGGL(k_node_stats, dim3(fill_grid(n)), dim3(BLOCK), 0, st, sig, acc, n, W, K, reached, dist_sum);
+hipError_t launch_node_stats(const uint64_t *sig, const int64_t *acc, const int32_t *perm, int64_t n, int W, int64_t K,
+                             int32_t *reached, int64_t *dist_sum, hipStream_t st) {
+    hipLaunchKernelGGL(k_node_stats, dim3(fill_grid(n)), dim3(BLOCK), 0, st, sig, acc, perm, n, W, K, reached, dist_sum);
     return hipGetLastError();
 }
 
