@@ -184,31 +184,47 @@ template <int W> PP_DEV void flush_lds(unsigned long long *dst, uint64_t (&acc)[
     }
 }
 
-// Per-seed counts, wave-wide: lane b accumulates how many lanes holding word
-// k have bit b set in d (lanes hold word lane % W).  Call with the whole
-// wave active.
-template <int W> PP_DEV void seed_ballot(uint64_t d, uint32_t (&sc)[W]) {
-    if (__ballot(d != 0) == 0) return;
+// The wave's 64 words as a 64 x 64 bit matrix, transposed: bit l of the result
+// in lane b is bit b of lane l's word.  Six exchanges of halves between lanes.
+PP_DEV uint64_t wave_transpose(uint64_t x) {
     const int ln = lane_id();
-    for (int bit = 0; bit < 64; ++bit) {
-        const uint64_t m = __ballot((int)((d >> bit) & 1ull));
-        if (m) {
 #pragma unroll
-            for (int k = 0; k < W; ++k) {
-                const uint32_t c = (uint32_t)__popcll(m & (WordMask<W>::rep << k));
-                if (ln == bit) sc[k] += c;
-            }
-        }
+    for (int j = 32; j > 0; j >>= 1) {
+        const uint64_t m = ~0ull / ((1ull << j) + 1ull);   // the bits whose index has j clear
+        const uint64_t y = __shfl_xor((unsigned long long)x, j);
+        x = (ln & j) ? (x & ~m) | ((y >> j) & m) : (x & m) | ((y << j) & ~m);
     }
+    return x;
 }
 
-template <int W> PP_DEV void seed_flush(const RunDev &R, int r, const uint32_t (&sc)[W]) {
-    const int ln = lane_id();
+// Per-seed counts, wave-wide: lane b accumulates how many lanes holding word
+// k have bit b set in d (lanes hold word lane % W).  Call with the whole
+// wave active.  By transposing the lanes' words and counting bits, about 70
+// instructions; a ballot per bit took about 700 (undirected R-MAT 17, s = 100,
+// per-seed counts: a pull 138 -> 130 us, see seed_flush for the rest).
+template <int W> PP_DEV void seed_ballot(uint64_t d, uint32_t (&sc)[W]) {
+    if (__ballot(d != 0) == 0) return;
+    const uint64_t t = wave_transpose(d);
 #pragma unroll
-    for (int k = 0; k < W; ++k) {
-        const int bitidx = k * 64 + ln;
-        if (sc[k] && bitidx < R.s) atomicAdd(&R.seed_counts[(int64_t)r * R.sstride + bitidx], sc[k]);
-    }
+    for (int k = 0; k < W; ++k) sc[k] += (uint32_t)__popcll(t & (WordMask<W>::rep << k));
+}
+
+// The block's per-seed counts into round r's row: its waves' sums meet in LDS, so
+// each seed takes one add per block (every block adds to the same few lines: with
+// one add per wave they queued for most of a pull, undirected R-MAT 17, s = 100:
+// 130 us per pull, 56 us with one per block).  Every thread of the block calls.
+template <int W> PP_DEV void seed_flush(const RunDev &R, int r, const uint32_t (&sc)[W]) {
+    __shared__ uint32_t s_sc[W * 64];
+    const int ln = lane_id();
+    __syncthreads();
+    for (int i = threadIdx.x; i < W * 64; i += BLOCK) s_sc[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+        if (sc[k]) atomicAdd(&s_sc[k * 64 + ln], sc[k]);
+    __syncthreads();
+    for (int i = threadIdx.x; i < W * 64; i += BLOCK)
+        if (s_sc[i] && i < R.s) atomicAdd(&R.seed_counts[(int64_t)r * R.sstride + i], s_sc[i]);
 }
 
 // Counts of a batch of graphs, combined over the wave before the atomics: the
@@ -231,32 +247,18 @@ PP_DEV void wave_add_keyed(unsigned long long *base, int key, unsigned long long
 }
 
 // Per-seed counts of a batch: lane ln holds word ln % W of a row of graph
-// gi, d its new bits; the lanes of one graph are counted per seed bit by
-// ballot and each seed with new bits takes one atomic.  Every lane of the
-// wave calls.
+// gi, d its new bits; the lanes of one graph are counted per seed bit and each
+// seed with new bits takes one atomic.  Every lane of the wave calls.
 template <int W> PP_DEV void seed_bits_keyed(const RunDev &R, int r, int gi, uint64_t d, bool valid) {
     const int ln = lane_id();
     uint64_t todo = __ballot(valid && d != 0);
     while (todo) {   // wave-uniform
         const int k = __shfl(gi, __builtin_ctzll(todo));
         const bool mine = valid && gi == k;
-        const uint64_t dm = mine ? d : 0ull;
-        uint64_t any = dm;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) any |= __shfl_xor(any, o);
         uint32_t c[W];
 #pragma unroll
         for (int w = 0; w < W; ++w) c[w] = 0;
-        while (any) {   // the seed bits set in any lane of the graph
-            const int b = __builtin_ctzll(any);
-            any &= any - 1;
-            const uint64_t m = __ballot((int)((dm >> b) & 1ull));
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const uint32_t cw = (uint32_t)__popcll(m & (WordMask<W>::rep << w));
-                if (ln == b) c[w] = cw;
-            }
-        }
+        seed_ballot<W>(mine ? d : 0ull, c);
         const int64_t base = (int64_t)r * R.sstride + (int64_t)k * R.sg;
 #pragma unroll
         for (int w = 0; w < W; ++w)
