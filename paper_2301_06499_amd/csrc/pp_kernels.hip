@@ -1960,6 +1960,7 @@ PP_DEV void phase_push(const GraphDev &g, const RunDev &R, int bid, int nb) {
         constexpr int CH = PushShape<W>::CHUNK;
         constexpr int IT = CH / SL;
         const int slot = ln / W;
+        const bool read_first = filter || (FLAT && nch >= PUSH_READ_CHUNKS);
         for (int64_t c = wave; c < nch; c += nwaves) {   // wave-uniform
             const Chunk cd = sel(R.chunks, pp)[c];
             const int32_t v = ids[cd.entry];
@@ -1977,7 +1978,7 @@ PP_DEV void phase_push(const GraphDev &g, const RunDev &R, int bid, int nb) {
                 dd[it] = d;
             }
             if constexpr (SPARSE) spull_slots<W, IT>(g, R, sig, r, k, kv, w, dd, bq, C, pn);
-            else push_slots<W, IT>(R, sig, r, k, kv, g.tcol, w, dd, bq, C, pn, filter);
+            else push_slots<W, IT>(R, sig, r, k, kv, g.tcol, w, dd, bq, C, pn, read_first);
         }
     }
     bq.flush(&C->lst[pn].nodes, sel(R.f_ids, pn), &s_qbase);
