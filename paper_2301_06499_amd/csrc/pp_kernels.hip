@@ -1515,13 +1515,13 @@ PP_DEV void phase_pull_lists(const GraphDev &g, const RunDev &R, int bid, int nb
 // to chunks (the round's list).
 template <int W>
 PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb, int64_t *parts = nullptr,
-                            const int32_t *hub_node = nullptr, int nhubs = 0) {
+                            const int32_t *hub_node = nullptr, int nhubs = 0, int pstride = POST_MAX) {
     Ctrl *C = R.ctrl;
     if (nhubs == 0) {
         if (parts && threadIdx.x == 0) {
-            PUT(parts[0 * POST_MAX + bid], (int64_t)0);
-            PUT(parts[1 * POST_MAX + bid], (int64_t)0);
-            PUT(parts[2 * POST_MAX + bid], (int64_t)0);
+            PUT(parts[0 * pstride + bid], (int64_t)0);
+            PUT(parts[1 * pstride + bid], (int64_t)0);
+            PUT(parts[2 * pstride + bid], (int64_t)0);
         }
         return;
     }
@@ -1580,9 +1580,9 @@ PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb,
     const unsigned long long ta = block_sum<unsigned long long>((unsigned long long)parcs, s_red);
     if (threadIdx.x == 0) {
         if (parts) {
-            PUT(parts[0 * POST_MAX + bid], (int64_t)tp);
-            PUT(parts[1 * POST_MAX + bid], (int64_t)tn);
-            PUT(parts[2 * POST_MAX + bid], (int64_t)ta);
+            PUT(parts[0 * pstride + bid], (int64_t)tp);
+            PUT(parts[1 * pstride + bid], (int64_t)tn);
+            PUT(parts[2 * pstride + bid], (int64_t)ta);
         } else {
             if (tp) atomicAdd((unsigned long long *)&C->hub_cnt, tp);
             if (tn) atomicAdd((unsigned long long *)&C->hub_nodes, tn);
@@ -2874,16 +2874,25 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
     const int64_t items = (int64_t)(chunked ? g.nhubs : CTL(C->lst[p].nodes)) * W;
     const int nb = post_blocks(items, (int)gridDim.x);
     if ((int)blockIdx.x >= nb) return;
+    // one block alone hands its sums over in LDS and takes no ticket: its round's
+    // end reads nothing else of this launch but what the wait below covers
+    // (10,000-node graph, 64 seeds: 188 -> 181 us; R-MAT 20: 580 -> 574)
+    const bool alone = nb == 1;
+    __shared__ int64_t s_parts[3];
+    int64_t *const parts = alone ? s_parts : R.post_part;
+    const int pstride = alone ? 1 : POST_MAX;
     if (mode == MODE_PULL)
-        phase_pull_hubs<W>(g, R, blockIdx.x, nb, R.post_part, chunked ? g.hub_node : sel(R.f_ids, p), (int)(items / W));
-    else phase_push_commit<W>(g, R, 0, blockIdx.x, nb, R.post_part, mode == MODE_SPULL);
+        phase_pull_hubs<W>(g, R, blockIdx.x, nb, parts, chunked ? g.hub_node : sel(R.f_ids, p), (int)(items / W), pstride);
+    else phase_push_commit<W>(g, R, 0, blockIdx.x, nb, parts, mode == MODE_SPULL, pstride);
     __shared__ int s_last;
-    wait_global_ops();
+    if (!alone || R.G > 1 || g.exit_ok) wait_global_ops();   // its counts and gained bits are atomics in memory
     __syncthreads();
-    if (threadIdx.x == 0) s_last = last_block(R.tickets, (int)blockIdx.x, nb);
-    __syncthreads();
-    if (!s_last) return;
-    phase_round_end<MLP ? INFER_BLOCK : INFER_NONE>(g, R, 0, g.pull_grid, R.post_part, nb);
+    if (!alone) {
+        if (threadIdx.x == 0) s_last = last_block(R.tickets, (int)blockIdx.x, nb);
+        __syncthreads();
+        if (!s_last) return;
+    }
+    phase_round_end<MLP ? INFER_BLOCK : INFER_NONE>(g, R, 0, g.pull_grid, parts, nb, false, pstride);
     if (mode == MODE_PULL && g.exit_ok) phase_exit_decide(g, R, r);
 }
 
