@@ -1074,7 +1074,8 @@ int reset_with_host_seeds(pp_run r, const int32_t *seeds) {
 }
 
 // One wait for the host copy of the control state: the control blocks, D,
-// and the count rows [staged, upto) (at most STAGE_ROWS of them).  The
+// and the count rows [staged, upto) (at most STAGE_ROWS of them) that every
+// control block still running has passed: a group can be behind another.  The
 // clustered engine keeps one control block per graph: the summary has the
 // largest round, converged when every graph has, and the flags of any.  A
 // seed outside its graph (device seed lists are checked by the device) is
@@ -1085,7 +1086,7 @@ int sync_state(pp_run r, int upto) {
     const int G = r->G;
     const int KG = r->k * G;
     const int nstage = r->pgrid ? G : (r->k > 1 ? KG : 1);
-    const int rows = std::max(0, std::min({upto, r->cap, r->staged + STAGE_ROWS}) - r->staged);
+    int rows = std::max(0, std::min({upto, r->cap, r->staged + STAGE_ROWS}) - r->staged);
     HIP_TRY(pp::launch_stage(r->dev.ctrl, (int64_t)sizeof(Ctrl) * nstage, r->dev.D, KG,
                              r->dev.counts + (int64_t)r->staged * KG, (int64_t)rows * KG, r->h_ctrl_dev, r->h_D_dev,
                              r->h_rows_dev, r->stream));
@@ -1097,6 +1098,7 @@ int sync_state(pp_run r, int upto) {
     for (int j = 0; j < nc; ++j) {
         const Ctrl &c = r->h_ctrl[(size_t)j * cstep];
         r->cur[(size_t)j] = c.cur & 1;
+        if (!c.converged) rows = std::min(rows, std::max(0, c.round - r->staged));   // rows counted in full
         if (j == 0) continue;
         r->host_ctrl.round = std::max(r->host_ctrl.round, c.round);
         r->host_ctrl.converged = r->host_ctrl.converged && c.converged;
@@ -1130,9 +1132,11 @@ int ensure_staged(pp_run r, int upto) {
     return PP_OK;
 }
 
-// c_g[row] of graph gi, summed over the seed groups (rows already staged).
+// c_g[row] of graph gi, summed over the seed groups (rows already staged; 0
+// for a row that some group has still to run).
 int64_t staged_count(pp_run r, int row, int gi) {
     int64_t c = 0;
+    if (row >= r->staged) return 0;
     const size_t base = (size_t)row * r->k * r->G;
     for (int j = 0; j < r->k; ++j) c += r->counts_host[base + (size_t)j * r->G + gi];
     return c;
