@@ -1614,17 +1614,30 @@ namespace {
 
 hipEvent_t slot_event(pp_run r, int i, int which) { return r->timing ? r->ev[(size_t)(2 * i + which)] : nullptr; }
 
-// k rounds; light: the light rounds that come first, however many, before them
+// Whether this run's batches take their rounds as steps of two launches.
+// (groups may then be a round apart: only where no round limit has to stop them together)
+bool by_steps(pp_run r, const GraphDev &gv, bool limited) {
+    return (gv.m < pp::STEP_MAX_ARCS || (gv.short_lists && r->W <= 2)) && !gv.exit_ok && !(limited && r->k > 1) &&
+           !r->timing && !r->dev.node_acc && !r->dev.sparse_pull && r->dev.pull_k != 2;
+}
+
+hipError_t launch_slot(pp_run r, const GraphDev &gv, bool steps, int i) {
+    if (steps) return pp::launch_step(gv, r->dev, r->stream);
+    return pp::launch_round(gv, r->dev, r->stream, slot_event(r, i, 0), slot_event(r, i, 1));
+}
+
+// k rounds at most (k steps); light: the light rounds that come first, however many, before them
 // (their number is not bounded by k).
-int launch_batch(pp_run r, int k, bool light) {
+int launch_batch(pp_run r, int k, bool light, bool limited) {
     GraphDev gv = graph_view(r->g, run_tiles(r), r->W);
+    const bool steps = by_steps(r, gv, limited);
     if (!r->opt.use_graph || (r->timing && !r->graph_events) || (light && k == 1)) {
         if (light) HIP_TRY(noted(r, pp::launch_light(gv, r->dev, r->stream)));
         for (int i = 0; i < k; ++i)
-            HIP_TRY(noted(r, pp::launch_round(gv, r->dev, r->stream, slot_event(r, i, 0), slot_event(r, i, 1))));
+            HIP_TRY(noted(r, launch_slot(r, gv, steps, i)));
         return PP_OK;
     }
-    const int key = light ? -k : k;
+    const int key = (light ? -k : k) * 2 + (steps ? 1 : 0);
     auto it = r->graphs.find(key);
     if (it == r->graphs.end()) {
         hipGraph_t graph = nullptr;
@@ -1632,14 +1645,14 @@ int launch_batch(pp_run r, int k, bool light) {
         HIP_TRY(hipStreamBeginCapture(r->stream, hipStreamCaptureModeThreadLocal));
         hipError_t le = light ? pp::launch_light(gv, r->dev, r->stream) : hipSuccess;
         for (int i = 0; i < k && le == hipSuccess; ++i)
-            le = pp::launch_round(gv, r->dev, r->stream, slot_event(r, i, 0), slot_event(r, i, 1));
+            le = launch_slot(r, gv, steps, i);
         hipError_t ce = hipStreamEndCapture(r->stream, &graph);
         if (le != hipSuccess && r->timing) {
             // events inside a capture are not supported here: time direct launches instead
             if (graph) (void)hipGraphDestroy(graph);
             (void)hipGetLastError();
             r->graph_events = false;
-            return launch_batch(r, k, light);
+            return launch_batch(r, k, light, limited);
         }
         if (le != hipSuccess) return fail(PP_EDEVICE, "round capture: %s", hipGetErrorString(le));
         if (ce != hipSuccess) return fail(PP_EDEVICE, "end capture: %s", hipGetErrorString(ce));
@@ -1704,7 +1717,7 @@ extern "C" int pp_propagate_until_converged(pp_run r, int32_t max_rounds, int64_
             k = p;
         }
         const int before = r->host_ctrl.round;
-        int rc = launch_batch(r, k, light);
+        int rc = launch_batch(r, k, light, limit < r->cap - 1);
         if (rc) return rc;
         launched += k;
         if ((rc = sync_state(r, before + k))) return rc;

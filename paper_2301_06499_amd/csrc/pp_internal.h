@@ -117,7 +117,9 @@ struct Ctrl {
     uint64_t gain[8];     // seed bits that any node gained in the pull round being run
     uint64_t live[8];     // seed bits that any node gained in round exit_round - 1
     int32_t exit_round;   // this round, if it pulls, stops each node's list early (0: none)
-    int32_t pad_exit;
+    int32_t listed;       // the round whose frontier a step's listing has written (0: none)
+    int32_t step;         // 1: the step about to close listed a frontier, and no round ran
+    int32_t pad_step;
 };
 
 static_assert(sizeof(Ctrl) % 4 == 0, "the control block is staged to the host as 32-bit words");
@@ -221,6 +223,14 @@ constexpr int64_t EXIT_MIN_ARCS = (int64_t)1 << 20;
 // with eight words and 0.82 ms with four, pull 0.46 and 0.26 ms; the round after
 // that, 0.4% changed, is a push either way; 16 and 64 measure the same)
 constexpr float EXIT_PULL_SHARE = 16;
+// graphs of fewer arcs run their rounds as steps of two launches, as do those
+// whose pulls take the short-list form with any number of arcs: three launches
+// cost 1-3 us more per round (10,000-node graph of 100,000 arcs, 64 seeds: 184
+// -> 174 us; 301^2 lattice 4.80 -> 4.53 ms; 13-scale R-MAT, 512 seeds in two
+// groups: 0.99 -> 0.94 ms; 4096^2 lattice, 60M arcs, 128 seeds: 99.3 -> 96.9).
+// Larger graphs with long lists have their pushes' occupancy to lose (the
+// joint kernel's registers halve it) or early-exit pulls of three launches.
+constexpr int64_t STEP_MAX_ARCS = EXIT_MIN_ARCS;
 // blocks of the launch that take part (half of them with eight-word rows):
 // as many as are resident at once, since each block's start and sums cost more
 // than its share of a late round (R-MAT 24, eight words, the third pull: 1175
@@ -394,6 +404,11 @@ enum SparseKinds : int { SPARSE_BY_RUN = 0, SPARSE_PUSH = 1, SPARSE_PULL = 2, SP
 // One round; when e0/e1 are given they are recorded around the pull launch.
 hipError_t launch_round(const GraphDev &g, const RunDev &r, hipStream_t st, hipEvent_t e0 = nullptr,
                         hipEvent_t e1 = nullptr, int kinds = SPARSE_BY_RUN);
+// One step of a round in two launches: the round, or the listing of the
+// frontier before a push that follows a pull (then the round is the next step).
+// For runs with neither sparse pulls nor per-node sums, on graphs without
+// early-exit pulls, whose tiling is the default one.
+hipError_t launch_step(const GraphDev &g, const RunDev &r, hipStream_t st);
 // The light rounds at the head of a batch (one graph, no round limit below the
 // log's capacity, rounds not timed one by one).
 hipError_t launch_light(const GraphDev &g, const RunDev &r, hipStream_t st);

@@ -2735,7 +2735,7 @@ k_pull(GraphDev g, RunDev R0) {
             const int nb = exit_blocks(gridDim.x, W);
             if (blockIdx.x < nb) phase_pull_exit<W>(g, R, blockIdx.x, nb);
         } else phase_pull<W, KK, DEAD>(g, R, blockIdx.x, gridDim.x);
-    } else if (C->prev_mode == MODE_PULL && blockIdx.x < FRONTIER_BLOCKS) {
+    } else if (C->prev_mode == MODE_PULL && C->listed != C->round && blockIdx.x < FRONTIER_BLOCKS) {
         const int nb = gridDim.x < FRONTIER_BLOCKS ? (int)gridDim.x : FRONTIER_BLOCKS;
         phase_frontier<W, 1024>(g, R, blockIdx.x, nb);
     }
@@ -2754,7 +2754,7 @@ k_pull_short(GraphDev g, RunDev R0) {
     }
     if (C->mode == MODE_PULL) {
         phase_pull_lists<W>(g, R, blockIdx.x, gridDim.x);
-    } else if (C->prev_mode == MODE_PULL && blockIdx.x < FRONTIER_BLOCKS) {
+    } else if (C->prev_mode == MODE_PULL && C->listed != C->round && blockIdx.x < FRONTIER_BLOCKS) {
         const int nb = gridDim.x < FRONTIER_BLOCKS ? (int)gridDim.x : FRONTIER_BLOCKS;
         phase_frontier<W, 1024>(g, R, blockIdx.x, nb);
     }
@@ -2765,6 +2765,36 @@ template <int W> __global__ void __launch_bounds__(BLOCK) k_push(GraphDev g, Run
     if (R.ctrl->converged) return;
     if (mode == MODE_PUSH) phase_push<W>(g, R, blockIdx.x, gridDim.x);
     else if (mode == MODE_PULL && exits(g, R.ctrl, R.ctrl->round)) phase_pull_rest<W>(g, R, blockIdx.x, gridDim.x);
+}
+// A round in two launches, this one and the closing one: the
+// pull, or the push; a push that follows a pull first lists the frontier, in a
+// step of its own.  Such a round is bound by its launches, so one fewer is
+// worth more than the occupancy that the phases' joint registers and LDS cost
+// (STEP_MAX_ARCS has the figures).
+template <int W, bool SHORT>
+__global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W >= 8 ? 2 : PP_PULL_WAVES)))
+k_step(GraphDev g, RunDev R0, int push_blocks) {
+    const RunDev R = group_view(R0, blockIdx.y);
+    Ctrl *C = R.ctrl;
+    if (C->converged) return;
+    const int r = C->round;
+    const bool pull = C->mode == MODE_PULL, after_pull = C->prev_mode == MODE_PULL, listed = C->listed == r;
+    const bool list = !pull && after_pull && !listed;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        // the round's start: its first launch's first block
+        if ((pull || !after_pull || list) && r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
+        C->step = list ? 1 : 0;   // read by the closing launch only
+    }
+    if (pull) {
+        if ((int)blockIdx.x >= g.pull_grid) return;
+        if constexpr (SHORT) phase_pull_lists<W>(g, R, blockIdx.x, g.pull_grid);
+        else phase_pull<W>(g, R, blockIdx.x, g.pull_grid);
+    } else if (list) {
+        const int nb = (int)gridDim.x < FRONTIER_BLOCKS ? (int)gridDim.x : FRONTIER_BLOCKS;
+        if ((int)blockIdx.x < nb) phase_frontier<W, 1024>(g, R, blockIdx.x, nb);
+    } else if ((int)blockIdx.x < push_blocks) {
+        phase_push<W>(g, R, blockIdx.x, push_blocks);
+    }
 }
 // The sparse pull's kernel, apart from the push's so that a run that never
 // takes it keeps the push kernel's smaller register and LDS footprint.
@@ -2858,7 +2888,9 @@ PP_DEV bool last_block(int32_t *tickets, int bid, int nb) {
 // back every dirty L2 line, which this launch's plain writes (rows, deltas,
 // lists) need only at the launch boundary: up to 12 us per round on large
 // commits.
-template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(GraphDev g, RunDev R0) {
+// steps: the launch closes a k_step, which may have listed a frontier only; its
+// first block then notes the listing (no block of this launch reads the note).
+template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(GraphDev g, RunDev R0, int steps) {
     const RunDev R = group_view(R0, blockIdx.y);
     Ctrl *C = R.ctrl;
     if (CTL(C->converged)) {   // set only by the last block, after every block has finished
@@ -2870,6 +2902,10 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
     // the rest leave at once and take no ticket, so a small round's end does
     // not wait for the whole grid to count off
     const int r = CTL(C->round), p = r & 1;
+    if (steps && CTL(C->step)) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) C->listed = r;
+        return;
+    }
     const bool chunked = mode == MODE_PULL && !exits(g, C, r);   // high-degree nodes; else the round's list
     const int64_t items = (int64_t)(chunked ? g.nhubs : CTL(C->lst[p].nodes)) * W;
     const int nb = post_blocks(items, (int)gridDim.x);
@@ -3288,10 +3324,37 @@ static hipError_t round_impl(const GraphDev &g, const RunDev &R, hipStream_t st,
     }
     if (kinds & SPARSE_PUSH) hipLaunchKernelGGL(k_push<W>, dim3(push_grid(g), ng), dim3(BLOCK), 0, st, g, R);
     if (kinds & SPARSE_PULL) hipLaunchKernelGGL(k_spull<W>, dim3(push_grid(g), ng), dim3(BLOCK), 0, st, g, R);
-    if (R.sched == PP_SCHED_MLP) hipLaunchKernelGGL((k_post<W, true>), dim3(post_grid(g), ng), dim3(BLOCK), 0, st, g, R);
-    else hipLaunchKernelGGL((k_post<W, false>), dim3(post_grid(g), ng), dim3(BLOCK), 0, st, g, R);
+    if (R.sched == PP_SCHED_MLP) hipLaunchKernelGGL((k_post<W, true>), dim3(post_grid(g), ng), dim3(BLOCK), 0, st, g, R, 0);
+    else hipLaunchKernelGGL((k_post<W, false>), dim3(post_grid(g), ng), dim3(BLOCK), 0, st, g, R, 0);
     if (R.node_acc) hipLaunchKernelGGL(k_node_acc<W>, dim3(list_grid(g), ng), dim3(BLOCK), 0, st, g, R);
     return hipGetLastError();
+}
+
+template <int W> static hipError_t step_impl(const GraphDev &g, const RunDev &R, hipStream_t st) {
+    if (R.sparse_pull || R.node_acc || R.pull_k == 2 || g.exit_ok) return hipErrorInvalidValue;
+    const unsigned ng = (unsigned)R.ngroups;
+    const int pb = push_grid(g);
+    const dim3 grid(pb > g.pull_grid ? pb : g.pull_grid, ng);
+    bool short_form = false;
+    if constexpr (W <= 2) short_form = g.short_lists;
+    if (short_form) {
+        if constexpr (W <= 2) hipLaunchKernelGGL((k_step<W, true>), grid, dim3(BLOCK), 0, st, g, R, pb);
+    } else {
+        hipLaunchKernelGGL((k_step<W, false>), grid, dim3(BLOCK), 0, st, g, R, pb);
+    }
+    if (R.sched == PP_SCHED_MLP) hipLaunchKernelGGL((k_post<W, true>), dim3(post_grid(g), ng), dim3(BLOCK), 0, st, g, R, 1);
+    else hipLaunchKernelGGL((k_post<W, false>), dim3(post_grid(g), ng), dim3(BLOCK), 0, st, g, R, 1);
+    return hipGetLastError();
+}
+
+hipError_t launch_step(const GraphDev &g, const RunDev &R, hipStream_t st) {
+    switch (R.W) {
+        case 1: return step_impl<1>(g, R, st);
+        case 2: return step_impl<2>(g, R, st);
+        case 4: return step_impl<4>(g, R, st);
+        case 8: return step_impl<8>(g, R, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_seed_init(const GraphDev &g, const RunDev &R, const int32_t *seeds, const int32_t *map,
