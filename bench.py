@@ -10,10 +10,12 @@ paper does not time graph loading either); the seed list is already in HBM.
 Metric: edge-words OR'd per second, full-scan accounting: every executed
 round (D + 1 of them) is credited with m arcs x s/64 words, as Algorithm 1
 scans every arc every round.  The edge-words the kernels actually touched
-(push rounds touch only the frontier's arcs) are reported beside it.
+(push rounds touch only the frontier's arcs) are reported beside it; a pull
+that stops lists early is counted there with every arc, as an upper bound.
 
-Prints one JSON line.  `roofline` covers the dense pull kernel (HIP events
-around each launch, on the run's stream, over the timed steps);
+Prints one JSON line.  `roofline` covers the dense pull kernel's launches that
+walk every list (HIP events around each, on the run's stream, over the timed
+steps);
 `cpu_baseline` times the CPU oracle (one BFS per seed, all host cores) on
 the same workload.
 """
@@ -405,11 +407,19 @@ def bench_propagate_s(args, torch, pp, g, seeds, cfg):
     exact = want["D"] == D and list(want["counts"]) == list(counts)
     rounds = D + 1
     nominal = float(G.arcs) * (s / 64.0) * rounds
-    nw = (g.n + 63) // 64
-    # per examined arc its 4-byte successor id and the 8-byte signature word
-    # holding the successor's bit; per pass and seed every word read and written
-    bytes_total = examined * 12.0 + rounds * s * nw * 16.0
-    achieved = bytes_total / t / 1e9
+    # with fewer than eight seeds in flight: per examined arc its 4-byte successor
+    # id and the 8-byte signature word holding the successor's bit; per pass and
+    # seed every word read and written.  With more, the node-major passes read an
+    # id and a row once for all seeds in flight, and an arc examined for one seed
+    # has no bytes of its own: no figure
+    roof = None
+    if (args.concurrent or min(s, 256)) < 8:
+        bytes_total = examined * 12.0 + rounds * s * ((g.n + 63) // 64) * 16.0
+        achieved = bytes_total / t / 1e9
+        roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": 8000.0, "unit": "GB/s",
+                "frac": round(achieved / 8000.0, 4), "traffic": None, "kernel": "k_seq_pass",
+                "bytes_per_step": bytes_total,
+                "timing": "host clock around the synchronous call (every pass launch and check included)"}
     out = {"metric": "edge-words OR'd/sec (edges x s/64 per round), PROPAGATE-S", "value": nominal / t,
            "unit": "edge-words/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
            "ms_per_step": round(t * 1000.0, 4), "ms_per_step_min": round(min(times) * 1000.0, 4),
@@ -419,10 +429,7 @@ def bench_propagate_s(args, torch, pp, g, seeds, cfg):
            "arcs_examined": int(examined),
            "arcs_examined_per_s": examined / t,
            "full_scan_arcs": int(G.arcs) * rounds * s,
-           "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": 8000.0, "unit": "GB/s",
-                        "frac": round(achieved / 8000.0, 4), "traffic": None, "kernel": "k_seq_pass",
-                        "bytes_per_step": bytes_total,
-                        "timing": "host clock around the synchronous call (every pass launch and check included)"},
+           "roofline": roof,
            "check": {"against": "oracle per-seed BFS, every seed", "result": "bit-exact" if exact else "MISMATCH"}}
     print(json.dumps(out), flush=True)
     G.free()
@@ -568,7 +575,9 @@ def step_figures(args, pp, T, m, n, s, wl, opts):
     """Throughput, roofline of the dense pull launches and the round record of one timed run.
 
     Each round's pull launch covers every seed group; its algorithmic bytes are
-    those of the groups that pulled in that round (group logs), per group
+    those of the groups that pulled in that round (group logs).  A pull after a
+    pull may stop lists early on a large graph (one of 2^20 arcs or more that is
+    not all short lists), so there only pulls after another round count, per group
       per arc gathered: 4 B column index + 8Wg B source row
       per node: 8 B row offset (int64) + 8Wg B own row read + 8Wg B new row written."""
     rounds = T["D"] + 1
@@ -576,10 +585,12 @@ def step_figures(args, pp, T, m, n, s, wl, opts):
     by_reach = bool(opts.seed_groups == pp.PP_GROUPS_BY_REACH)
     nominal = m * (s / 64.0) * rounds
     touched = sum(float(a[1:rounds + 1].sum()) * Wg for _, a in T["logs"])
+    may_stop = m >= 1 << 20 and T["form"] != "short" and not opts.persistent
     pull_rounds, bytes_pull = [], 0.0
     for r in range(1, rounds + 1):
         pulled = [float(a[r]) for md, a in T["logs"] if md[r] == pp.MODE_PULL]
-        if pulled:
+        after_pull = any(md[r] == pp.MODE_PULL and md[r - 1] == pp.MODE_PULL for md, _ in T["logs"])
+        if pulled and not (may_stop and after_pull):
             pull_rounds.append(r)
             bytes_pull += sum(x * (4 + 8 * Wg) + n * (8 + 16 * Wg) for x in pulled)
     t_pull = sum(T["pull_ms"][r] for r in pull_rounds) / 1000.0
