@@ -963,9 +963,9 @@ int alloc_run_dev(pp_graph g, RunDev &d, int s_all, int k, int sg, int W, int ca
     return PP_OK;
 }
 
-// clean: per seed group, whether only its seeds' rows (prev_seeds, stored
-// ids, sg per group) can hold bits; those groups clear just those rows.
-// stale1: the other groups clear their first buffer in full and, in the
+// clean (only with stale1): per seed group, whether only its seeds' rows
+// (prev_seeds, stored ids, sg per group) can hold bits; those groups clear
+// just those rows.  stale1: the other groups clear their first buffer in full and, in the
 // second, only those rows.  That is enough because the second buffer is
 // read only after a pull has made it current, and a pull writes every row
 // there except those of nodes without successors, which no round changes:
@@ -979,22 +979,15 @@ hipError_t clear_run_dev(pp_graph g, RunDev &d, hipStream_t st, bool with_acc,
     const int64_t cap = d.cap;
     auto seg = [](void *p, int64_t bytes, uint32_t v) { return pp::FillSeg{(uint32_t *)p, bytes / 4, v}; };
     std::vector<pp::FillSeg> rows;   // signature rows and stamps, then the rest: one fill launch
-    bool some_clean = false;
-    for (char c : clean) some_clean |= c != 0;
-    if (!prev_seeds || (!some_clean && !stale1)) {
+    if (!prev_seeds || !stale1) {
         rows.push_back(seg(d.sig[0], 2 * 8 * k * n * d.W, 0u));  // both signature buffers of every group
         rows.push_back(seg(d.stamp, 4 * k * n, 0xFFFFFFFFu));    // -1: never queued
     } else {
         for (int64_t j = 0; j < k; ++j) {
             uint64_t *sj = d.sig[0] + j * 2 * n * d.W;
             const bool cj = (size_t)j < clean.size() && clean[(size_t)j];
-            if (cj || stale1) {   // the seeds' rows in both buffers (the fill below runs after)
-                const int cnt = j == k - 1 ? d.s_last : d.sg;
-                const hipError_t e = pp::launch_clear_seed_rows(prev_seeds + j * d.sg, cnt, n, d.W, sj, d.stamp + j * n, st);
-                if (e != hipSuccess) return e;
-            }
             if (!cj) {
-                rows.push_back(seg(sj, (stale1 ? 1 : 2) * 8 * n * d.W, 0u));
+                rows.push_back(seg(sj, 8 * n * d.W, 0u));
                 rows.push_back(seg(d.stamp + j * n, 4 * n, 0xFFFFFFFFu));
             }
         }
@@ -1015,7 +1008,8 @@ hipError_t clear_run_dev(pp_graph g, RunDev &d, hipStream_t st, bool with_acc,
         seg(d.node_acc, d.node_acc ? 8 * n : 0, 0u),
     };
     rows.insert(rows.end(), std::begin(rest), std::end(rest));
-    return pp::launch_fills(rows.data(), (int)rows.size(), st);
+    const pp::SeedRows seed_rows{prev_seeds, d.sig[0], d.stamp, n, d.sg, d.s_last, (int32_t)k, d.W};
+    return pp::launch_fills(rows.data(), (int)rows.size(), st, prev_seeds && stale1 ? &seed_rows : nullptr);
 }
 
 TileSet *run_tiles(pp_run r) { return &r->g->tiles[pull_edges(r->W, r->dev.pull_k)]; }
@@ -1270,7 +1264,7 @@ int reset_run(pp_run r, const int32_t *seeds, const int32_t *map) {
             // the seed list in internal order (stored ids), then the groups' seed bits
             e = pp::launch_seed_order(gv, seeds, map, r->G, r->s, r->opt.seed_order == PP_ORDER_BY_REACH, r->iseeds,
                                       r->dpos, r->stream);
-            if (e == hipSuccess) e = pp::launch_seed_init(gv, r->dev, r->iseeds, nullptr, r->stream);
+            if (e == hipSuccess) e = pp::launch_seed_init(gv, r->dev, r->iseeds, nullptr, nullptr, r->stream);
         } else if (r->pgrid) {
             if (map) {
                 e = pp::launch_map_ids(r->dseeds, seeds, map, (int64_t)r->G * r->s, g->n, r->stream);
@@ -1278,12 +1272,8 @@ int reset_run(pp_run r, const int32_t *seeds, const int32_t *map) {
             }
             if (e == hipSuccess) e = pp::launch_seed_scatter_batch(gv, r->dev, seeds, r->stream);
         } else {
-            e = pp::launch_seed_init(gv, r->dev, seeds, map, r->stream);
-            if (e == hipSuccess && plain1) {
-                e = map ? pp::launch_map_ids(r->dseeds, seeds, map, r->s, g->n, r->stream)
-                        : hipMemcpyAsync(r->dseeds, seeds, sizeof(int32_t) * (size_t)r->s, hipMemcpyDefault, r->stream);
-                r->seeds_kept = e == hipSuccess;
-            }
+            e = pp::launch_seed_init(gv, r->dev, seeds, map, plain1 ? r->dseeds : nullptr, r->stream);
+            r->seeds_kept = plain1 && e == hipSuccess;
         }
     }
     if (e != hipSuccess) return fail(PP_EDEVICE, "seed initialisation: %s", hipGetErrorString(e));

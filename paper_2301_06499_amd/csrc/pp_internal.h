@@ -320,13 +320,19 @@ struct FillSeg {
     int64_t n;
     uint32_t v;
 };
-// Every segment in as few launches as possible (one for up to 16 segments).
-hipError_t launch_fills(const FillSeg *segs, int nseg, hipStream_t st);
-// One seed group's rows and stamps back to the initial state when only its
-// seeds' rows can hold bits: ids [count] stored ids, sig the group's two
-// buffers (n rows of W words each, one after the other), stamp its n stamps.
-hipError_t launch_clear_seed_rows(const int32_t *ids, int count, int64_t n, int W, uint64_t *sig, int32_t *stamp,
-                                  hipStream_t st);
+// The rows (in both buffers) and stamps of every seed group's seeds: ids stored
+// ids, sg per group (s_last in the last), sig a group's two buffers of n rows
+// of W words one after the other, stamp n per group.
+struct SeedRows {
+    const int32_t *ids;
+    uint64_t *sig;
+    int32_t *stamp;
+    int64_t n;
+    int32_t sg, s_last, groups, W;
+};
+// Every segment in as few launches as possible (one for up to 32 segments),
+// and rows (may be NULL) back to their initial state beside them.
+hipError_t launch_fills(const FillSeg *segs, int nseg, hipStream_t st, const SeedRows *rows = nullptr);
 // out[j] = perm[in[j]] (ids outside [0, n) become -1).
 hipError_t launch_map_ids(int32_t *out, const int32_t *in, const int32_t *perm, int64_t count, int64_t n,
                           hipStream_t st);
@@ -397,7 +403,7 @@ hipError_t launch_sig_regroup(const uint64_t *sig, int64_t n, int Wg, int Wout, 
                               uint64_t *out, hipStream_t st);
 // seeds: device-readable ids; map (may be NULL): input id -> stored id.
 hipError_t launch_seed_init(const GraphDev &g, const RunDev &r, const int32_t *seeds, const int32_t *map,
-                            hipStream_t st);
+                            int32_t *keep, hipStream_t st);
 // Sparse-round kernels a round launches: the push's, the sparse pull's, or
 // both (SPARSE_BY_RUN: as the run's sparse_pull option asks).
 enum SparseKinds : int { SPARSE_BY_RUN = 0, SPARSE_PUSH = 1, SPARSE_PULL = 2, SPARSE_BOTH = 3 };

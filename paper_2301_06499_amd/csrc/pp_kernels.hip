@@ -399,16 +399,44 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t count, hipStream_t st)
 
 // Several fills in one launch: block b fills chunk b - first_block[k] of
 // segment k (FILL_CHUNK 4-byte words; 16-byte stores for whole quadruples).
-constexpr int FILL_SEGS = 16;
+// The blocks behind the last segment's clear seed rows (SeedRows): a launch of
+// its own per seed group cost a reset 4-8 us each, more than either's work
+// (R-MAT 13 in 16 groups of 512 seeds: 929 -> 892 us per call; 10,000-node graph,
+// 64 seeds: 171 -> 166 us; R-MAT 20: 583 -> 571 us).
+constexpr int FILL_SEGS = 32;
 constexpr int64_t FILL_CHUNK = (int64_t)BLOCK * 16;
 struct FillPlan {
     FillSeg seg[FILL_SEGS];
     int64_t first_block[FILL_SEGS + 1];
     int32_t nseg;
+    SeedRows rows;
 };
+static_assert(sizeof(FillPlan) <= 4096, "kernel arguments");
+
+// Seed group j's rows (both buffers) and stamps of its seeds' stored ids back to
+// their initial state, one seed per thread: blocks [0, blocks per group) are
+// group 0's.  Ids outside [0, n) are skipped.
+PP_DEV void clear_seed_rows(const SeedRows &S, int64_t bid) {
+    const int64_t per = (S.sg + BLOCK - 1) / BLOCK;
+    const int64_t j = bid / per;
+    const int64_t i = (bid - j * per) * BLOCK + threadIdx.x;
+    if (i >= (j == S.groups - 1 ? S.s_last : S.sg)) return;
+    const int32_t x = S.ids[j * S.sg + i];
+    if (x < 0 || x >= S.n) return;
+    uint64_t *sig = S.sig + j * 2 * S.n * S.W;
+    for (int w = 0; w < S.W; ++w) {
+        sig[(int64_t)x * S.W + w] = 0;
+        sig[S.n * S.W + (int64_t)x * S.W + w] = 0;
+    }
+    S.stamp[j * S.n + x] = -1;
+}
 
 __global__ void __launch_bounds__(BLOCK) k_fill_plan(FillPlan P) {
     const int64_t b = blockIdx.x;
+    if (b >= P.first_block[P.nseg]) {
+        clear_seed_rows(P.rows, b - P.first_block[P.nseg]);
+        return;
+    }
     int k = 0;
     while (k + 1 < P.nseg && P.first_block[k + 1] <= b) ++k;
     const FillSeg S = P.seg[k];
@@ -420,14 +448,19 @@ __global__ void __launch_bounds__(BLOCK) k_fill_plan(FillPlan P) {
     for (int64_t i = body + threadIdx.x; i < w1; i += BLOCK) S.p[i] = S.v;
 }
 
-hipError_t launch_fills(const FillSeg *segs, int nseg, hipStream_t st) {
+hipError_t launch_fills(const FillSeg *segs, int nseg, hipStream_t st, const SeedRows *rows) {
     FillPlan P{};
     int k = 0;
     int64_t blocks = 0;
     auto flush = [&]() -> hipError_t {
-        if (k == 0) return hipSuccess;
+        if (k == 0 && !rows) return hipSuccess;
         P.nseg = k;
         P.first_block[k] = blocks;
+        if (rows) {   // with the first launch
+            P.rows = *rows;
+            blocks += (int64_t)rows->groups * ((rows->sg + BLOCK - 1) / BLOCK);
+            rows = nullptr;
+        }
         hipLaunchKernelGGL(k_fill_plan, dim3((unsigned)blocks), dim3(BLOCK), 0, st, P);
         P = FillPlan{};
         k = 0;
@@ -446,30 +479,6 @@ hipError_t launch_fills(const FillSeg *segs, int nseg, hipStream_t st) {
         ++k;
     }
     return flush();
-}
-
-// A seed group's rows back to their initial state where only its seeds can
-// have set bits: the rows of the given stored ids (both buffers) and their
-// stamps.  Ids outside [0, n) are skipped.
-__global__ void __launch_bounds__(BLOCK) k_clear_seed_rows(const int32_t *ids, int count, int64_t n, int W,
-                                                           uint64_t *sig, int32_t *stamp) {
-    for (int i = blockIdx.x * BLOCK + threadIdx.x; i < count; i += gridDim.x * BLOCK) {
-        const int32_t x = ids[i];
-        if (x < 0 || x >= n) continue;
-        for (int w = 0; w < W; ++w) {
-            sig[(int64_t)x * W + w] = 0;
-            sig[n * W + (int64_t)x * W + w] = 0;
-        }
-        stamp[x] = -1;
-    }
-}
-
-hipError_t launch_clear_seed_rows(const int32_t *ids, int count, int64_t n, int W, uint64_t *sig, int32_t *stamp,
-                                  hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_clear_seed_rows, dim3((count + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, st, ids, count, n, W,
-                       sig, stamp);
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- node ids
@@ -681,9 +690,11 @@ hipError_t launch_sig_regroup(const uint64_t *sig, int64_t n, int Wg, int Wout, 
 // seed outside its graph's node range is skipped and flagged.
 // map (may be NULL): input id -> stored id for ids in [0, n), -1 otherwise.
 // seeds: the group's first seed of graph 0 (graph gi's at gi * s_all).
+// keep (may be NULL; one graph without groups): the stored ids, for the next
+// reset (a copy of its own cost a launch).
 template <int W>
 PP_DEV void phase_seed_scatter(const GraphDev &g, const RunDev &R, const int32_t *seeds, const int32_t *map,
-                               int bid, int nb) {
+                               int bid, int nb, int32_t *keep = nullptr) {
     const int64_t total = (int64_t)R.G * R.s;
     for (int64_t j = bid * (int64_t)BLOCK + threadIdx.x; j < total; j += (int64_t)nb * BLOCK) {
         const int i = (int)(j % R.s);
@@ -692,6 +703,7 @@ PP_DEV void phase_seed_scatter(const GraphDev &g, const RunDev &R, const int32_t
         if (map) x = (x >= 0 && x < g.n) ? map[x] : -1;
         const bool ok = x >= g.node_off[gi] && x < g.node_off[gi + 1];
         if (!ok) atomicOr(&R.ctrl->bad_seed, 1);
+        if (keep) keep[j] = x;
         if (ok) atomicOr((unsigned long long *)&R.acc[(int64_t)x * W + (i >> 6)], 1ull << (i & 63));
         const bool want = ok && atomicMax(&R.stamp[x], 0) < 0;
         const int pos = wave_append(&R.ctrl->lst[0].nodes, want);
@@ -2827,9 +2839,10 @@ template <int W> __global__ void __launch_bounds__(LIGHT_THREADS) k_light(GraphD
 // block's barriers order them; its global writes are visible to its own
 // threads after a barrier).
 template <int W>
-__global__ void __launch_bounds__(BLOCK) k_seed_init(GraphDev g, RunDev R0, const int32_t *seeds, const int32_t *map) {
+__global__ void __launch_bounds__(BLOCK) k_seed_init(GraphDev g, RunDev R0, const int32_t *seeds, const int32_t *map,
+                                                    int32_t *keep) {
     const RunDev R = group_view(R0, blockIdx.y);
-    phase_seed_scatter<W>(g, R, seeds + (int64_t)blockIdx.y * R0.sg, map, 0, 1);
+    phase_seed_scatter<W>(g, R, seeds + (int64_t)blockIdx.y * R0.sg, map, 0, 1, keep);
     __syncthreads();
     phase_push_commit<W>(g, R, 1, 0, 1);
     __syncthreads();
@@ -3281,14 +3294,15 @@ constexpr int64_t SEED_INIT_ONE_BLOCK = 4096;
 
 template <int W>
 static hipError_t seed_init_impl(const GraphDev &g, const RunDev &R, const int32_t *seeds, const int32_t *map,
-                                 hipStream_t st) {
+                                 int32_t *keep, hipStream_t st) {
     const int64_t total = (int64_t)R.G * R.sg;   // seeds of the largest group
     const unsigned ng = (unsigned)R.ngroups;
     if (total <= SEED_INIT_ONE_BLOCK) {
-        hipLaunchKernelGGL(k_seed_init<W>, dim3(1, ng), dim3(BLOCK), 0, st, g, R, seeds, map);
+        hipLaunchKernelGGL(k_seed_init<W>, dim3(1, ng), dim3(BLOCK), 0, st, g, R, seeds, map, keep);
         if (R.node_acc) hipLaunchKernelGGL(k_node_acc<W>, dim3(list_grid(g), ng), dim3(BLOCK), 0, st, g, R);
         return hipGetLastError();
     }
+    if (keep) return hipErrorInvalidValue;   // one graph's list is never that long
     hipLaunchKernelGGL(k_seed_scatter<W>, dim3(fill_grid(total), ng), dim3(BLOCK), 0, st, g, R, seeds, map);
     hipLaunchKernelGGL(k_push_commit<W>, dim3(fill_grid(total * W), ng), dim3(BLOCK), 0, st, g, R, 1);
     hipLaunchKernelGGL(k_round_end, dim3(1, ng), dim3(BLOCK), 0, st, g, R, 1);
@@ -3358,12 +3372,12 @@ hipError_t launch_step(const GraphDev &g, const RunDev &R, hipStream_t st) {
 }
 
 hipError_t launch_seed_init(const GraphDev &g, const RunDev &R, const int32_t *seeds, const int32_t *map,
-                            hipStream_t st) {
+                            int32_t *keep, hipStream_t st) {
     switch (R.W) {
-        case 1: return seed_init_impl<1>(g, R, seeds, map, st);
-        case 2: return seed_init_impl<2>(g, R, seeds, map, st);
-        case 4: return seed_init_impl<4>(g, R, seeds, map, st);
-        case 8: return seed_init_impl<8>(g, R, seeds, map, st);
+        case 1: return seed_init_impl<1>(g, R, seeds, map, keep, st);
+        case 2: return seed_init_impl<2>(g, R, seeds, map, keep, st);
+        case 4: return seed_init_impl<4>(g, R, seeds, map, keep, st);
+        case 8: return seed_init_impl<8>(g, R, seeds, map, keep, st);
         default: return hipErrorInvalidValue;
     }
 }
