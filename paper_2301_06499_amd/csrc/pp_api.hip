@@ -1296,9 +1296,8 @@ int reset_run(pp_run r, const int32_t *seeds, const int32_t *map) {
 }
 
 // Splits the persistent grid among the graphs of a batch, in proportion to
-// their arcs plus nodes, at least one block each and at most one per 48 Ki
-// arcs plus nodes, only one up to 64 Ki (blocks beyond every cap stay idle);
-// graph order is kept.
+// their arcs plus nodes, at least one block each and at most one per 64 Ki
+// arcs plus nodes (blocks beyond every cap stay idle); graph order is kept.
 std::vector<pp::Cluster> make_clusters(pp_graph g, const TileSet *ts, int grid) {
     const int G = g->G;
     std::vector<double> w((size_t)G);
@@ -1308,17 +1307,15 @@ std::vector<pp::Cluster> make_clusters(pp_graph g, const TileSet *ts, int grid) 
         w[(size_t)k] = (double)(g->rp_host[(size_t)n1] - g->rp_host[(size_t)n0]) + (double)(n1 - n0) + 1.0;
         tot += w[(size_t)k];
     }
-    // a graph of up to CLUSTER_ONE arcs plus nodes runs on one block, which
-    // synchronises with its own barrier only and takes light rounds; a larger one
-    // gets at most one block per CLUSTER_ITEMS (lattice 512^2 alone 54.7 ms at 64
-    // Ki, 46.9 at 48 Ki, 40.4 at 32 Ki, 37.5 at 16 Ki, but every barrier drops
-    // its XCDs' L2 for the other clusters too: the 64-graph batch 68.3, 66.8, 74.5
-    // and 70.3 ms)
-    constexpr double CLUSTER_ITEMS = 49152.0, CLUSTER_ONE = 65536.0;
+    // a graph gets at most one block per CLUSTER_ITEMS arcs plus nodes: small
+    // graphs run many cheap rounds, where a barrier among a few blocks costs
+    // more than the work it spreads (one block synchronises with its own
+    // barrier only)
+    constexpr double CLUSTER_ITEMS = 65536.0;
     std::vector<int> nb((size_t)G, 1), cap((size_t)G);
     int used = G;
     for (int k = 0; k < G; ++k) {
-        cap[(size_t)k] = w[(size_t)k] <= CLUSTER_ONE ? 1 : (int)std::ceil(w[(size_t)k] / CLUSTER_ITEMS);
+        cap[(size_t)k] = (int)std::max(1.0, std::ceil(w[(size_t)k] / CLUSTER_ITEMS));
         const int extra = std::min((int)((double)(grid - G) * w[(size_t)k] / tot), cap[(size_t)k] - 1);
         nb[(size_t)k] += extra;
         used += extra;

@@ -3008,86 +3008,52 @@ hipError_t launch_redecide(const RunDev &R, int nctrl, int stride, hipStream_t s
 
 // ---------------------------------------------------------------- persistent rounds
 
-// Barrier among the nb blocks of one cluster (block rank bid); the last block to
-// arrive runs last() (whole block) before anyone goes on.  A cluster of one
-// block only needs the block barrier.  Otherwise blocks arrive on one of up to
-// eight group counters (rank i in group i % 8, matching the round-robin
-// placement of blocks on the XCDs), the last of a group arrives on the top
-// counter, and the last group advances the generation everyone waits on.
-// Each thread waits for its own global operations before the block's barrier
-// (which does not wait for them); one release by a block before it arrives
-// writes its XCD's L2 back, one acquire after it leaves drops stale lines: the
-// two are most of a barrier's time, so the counters in between are plain
-// device-scope atomics and a round's end runs inside the barrier before it
-// instead of between two (64-graph batch 82.9 -> 68.9 ms, its 21 lattices alone
-// 79.8 -> 64.1 ms).  A wait
-// longer than about ten seconds sets `abort`; every later barrier and the round
-// loop then return, so the grid always drains.
-template <typename F> PP_DEV bool cluster_barrier(GridBar *b, int bid, int nb, F last) {
-    __shared__ int s_abort, s_last;
-    if (nb == 1) {   // one block: nothing to wait for, and no one to time out
-        __syncthreads();
-        last();
-        __syncthreads();
-        return true;
-    }
-    wait_global_ops();
+// Barrier among the nb blocks of one cluster (block rank bid).  A cluster of
+// one block only needs the block barrier.  Otherwise blocks arrive on one of
+// up to eight group counters (rank i in group i % 8, matching the
+// round-robin placement of blocks on the XCDs), the last of a group arrives
+// on the top counter, and the last group advances the generation everyone
+// waits on.  The agent-scope fences publish each block's writes before it
+// arrives and make the others' writes visible after it leaves.  A wait longer
+// than about ten seconds sets `abort`; every later barrier and the round loop
+// then return, so the grid always drains.
+PP_DEV bool cluster_barrier(GridBar *b, int bid, int nb) {
+    __shared__ int s_abort;
     __syncthreads();
-    int ab = 0;
-    uint32_t gen = 0;
+    if (nb == 1) return true;   // one block: nothing to wait for, and no one to time out
     if (threadIdx.x == 0) {
         const uint32_t ng = nb < 8 ? (uint32_t)nb : 8u;
         const uint32_t grp = (uint32_t)bid % ng;
         const uint32_t gsize = (uint32_t)nb / ng + (grp < (uint32_t)nb % ng ? 1u : 0u);
-        ab = CTL(b->abort);
-        s_last = 0;
+        int ab = CTL(b->abort);
         if (!ab) {
-            gen = CTL(b->gen);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            const uint32_t gen = CTL(b->gen);
+            __threadfence();
             if (atomicAdd(&b->grp[grp], 1u) + 1 == gsize) {
-                atomicExch(&b->grp[grp], 0u);   // before anyone can arrive again: not before gen moves
-                wait_global_ops();
+                atomicExch(&b->grp[grp], 0u);
+                __threadfence();
                 if (atomicAdd(&b->top, 1u) + 1 == ng) {
                     atomicExch(&b->top, 0u);
-                    s_last = 1;
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    __threadfence();
+                    atomicAdd(&b->gen, 1u);
                 }
             }
-        }
-    }
-    __syncthreads();
-    const bool mine = s_last != 0;
-    if (mine) {   // block-uniform
-        last();
-        wait_global_ops();
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        if (!ab) {
-            if (mine) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                atomicAdd(&b->gen, 1u);
-            } else {
-                const uint64_t t0 = wall_clock64();
-                while (CTL(b->gen) == gen) {
-                    __builtin_amdgcn_s_sleep(2);
-                    if (wall_clock64() - t0 > 1000000000ull) {   // ~10 s at 100 MHz
-                        atomicExch(&b->abort, 1);
-                        break;
-                    }
-                    if (CTL(b->abort)) break;
+            const uint64_t t0 = wall_clock64();
+            while (CTL(b->gen) == gen) {
+                __builtin_amdgcn_s_sleep(2);
+                if (wall_clock64() - t0 > 1000000000ull) {   // ~10 s at 100 MHz
+                    atomicExch(&b->abort, 1);
+                    break;
                 }
+                if (CTL(b->abort)) break;
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            __threadfence();
             ab = CTL(b->abort);
         }
         s_abort = ab;
     }
     __syncthreads();
     return s_abort == 0;
-}
-PP_DEV bool cluster_barrier(GridBar *b, int bid, int nb) {
-    return cluster_barrier(b, bid, nb, [] {});
 }
 
 // The slice of a batch that one cluster runs: graph cl.g as a graph of its
@@ -3176,7 +3142,9 @@ k_batch(GraphDev g, RunDev R, const Cluster *clusters, int nclusters,
     bool ok = true;
     if (CTL(C->round) == 0 && !CTL(C->converged)) {
         phase_push_commit<W, 1>(gv, rv, 1, bid, nb);
-        ok = cluster_barrier(bar, bid, nb, [&] { phase_round_end(gv, rv, 1, nb, nullptr, 0, true); });
+        ok = cluster_barrier(bar, bid, nb);
+        if (ok && bid == 0) phase_round_end(gv, rv, 1, nb, nullptr, 0, true);
+        if (ok) ok = cluster_barrier(bar, bid, nb);
     }
     while (ok) {
         const int conv = CTL(C->converged);
@@ -3199,22 +3167,20 @@ k_batch(GraphDev g, RunDev R, const Cluster *clusters, int nclusters,
             if (!cluster_barrier(bar, bid, nb)) break;
             if (lead && stamp) stamp[1] = (int64_t)wall_clock64();
             phase_push_commit<W, 1>(gv, rv, 0, bid, nb, lparts, false, 1);
+            if (!cluster_barrier(bar, bid, nb)) break;
         } else {
             phase_pull<W>(gv, rv, bid, nb);
+            if (!cluster_barrier(bar, bid, nb)) break;
+            if (lead && stamp) stamp[1] = (int64_t)wall_clock64();
             if (gv.nhubs) {
-                if (!cluster_barrier(bar, bid, nb)) break;
-                if (lead && stamp) stamp[1] = (int64_t)wall_clock64();
                 phase_pull_hubs<W>(gv, rv, bid, nb, nullptr, gv.hub_node, gv.nhubs);
+                if (!cluster_barrier(bar, bid, nb)) break;
             }
         }
-        const bool end_main = mode == MODE_PULL && gv.nhubs == 0;   // the round's end closes the main phase
-        // the round's end, by the last block to finish
         const bool lp = local && mode == MODE_PUSH;
-        if (!cluster_barrier(bar, bid, nb, [&] {
-                if (end_main && stamp && threadIdx.x == 0) stamp[1] = (int64_t)wall_clock64();
-                phase_round_end(gv, rv, 0, nb, lp ? lparts : nullptr, lp ? 1 : 0, true, 1);
-            }))
-            break;
+        if (bid == 0) phase_round_end(gv, rv, 0, nb, lp ? lparts : nullptr, lp ? 1 : 0, true, 1);
+        if (lead && stamp) stamp[2] = (int64_t)wall_clock64();
+        if (!cluster_barrier(bar, bid, nb)) break;
     }
     if (local) {   // the control block back for the host and the next launch
         __syncthreads();
