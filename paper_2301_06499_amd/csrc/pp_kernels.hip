@@ -712,9 +712,9 @@ PP_DEV void phase_seed_scatter(const GraphDev &g, const RunDev &R, const int32_t
 }
 template <int W>
 __global__ void __launch_bounds__(BLOCK) k_seed_scatter(GraphDev g, RunDev R0, const int32_t *seeds,
-                                                        const int32_t *map) {
+                                                        const int32_t *map, int32_t *keep) {
     const RunDev R = group_view(R0, blockIdx.y);
-    phase_seed_scatter<W>(g, R, seeds + (int64_t)blockIdx.y * R0.sg, map, blockIdx.x, gridDim.x);
+    phase_seed_scatter<W>(g, R, seeds + (int64_t)blockIdx.y * R0.sg, map, blockIdx.x, gridDim.x, keep);
 }
 
 // ---------------------------------------------------------------- list commit
@@ -3255,21 +3255,25 @@ static int post_grid(const GraphDev &g) {
     return (int)(b < 64 ? 64 : (b > POST_MAX ? POST_MAX : b));
 }
 
-// seed lists up to this length initialise in one single-block launch
-constexpr int64_t SEED_INIT_ONE_BLOCK = 4096;
+// seed lists up to this many words (seeds times words per row) initialise in one
+// single-block launch; more take three launches of many blocks, since one
+// block commits 1024 words per pass of dependent loads, about 6 us each (R-MAT
+// 13, groups of 512 seeds and eight words: 897 -> 867 us per call for its two
+// initialisations; one block against three launches measures the same at 1024
+// words: R-MAT 20, 256 seeds)
+constexpr int64_t SEED_INIT_ONE_BLOCK = 2048;
 
 template <int W>
 static hipError_t seed_init_impl(const GraphDev &g, const RunDev &R, const int32_t *seeds, const int32_t *map,
                                  int32_t *keep, hipStream_t st) {
     const int64_t total = (int64_t)R.G * R.sg;   // seeds of the largest group
     const unsigned ng = (unsigned)R.ngroups;
-    if (total <= SEED_INIT_ONE_BLOCK) {
+    if (total * W <= SEED_INIT_ONE_BLOCK) {
         hipLaunchKernelGGL(k_seed_init<W>, dim3(1, ng), dim3(BLOCK), 0, st, g, R, seeds, map, keep);
         if (R.node_acc) hipLaunchKernelGGL(k_node_acc<W>, dim3(list_grid(g), ng), dim3(BLOCK), 0, st, g, R);
         return hipGetLastError();
     }
-    if (keep) return hipErrorInvalidValue;   // one graph's list is never that long
-    hipLaunchKernelGGL(k_seed_scatter<W>, dim3(fill_grid(total), ng), dim3(BLOCK), 0, st, g, R, seeds, map);
+    hipLaunchKernelGGL(k_seed_scatter<W>, dim3(fill_grid(total), ng), dim3(BLOCK), 0, st, g, R, seeds, map, keep);
     hipLaunchKernelGGL(k_push_commit<W>, dim3(fill_grid(total * W), ng), dim3(BLOCK), 0, st, g, R, 1);
     hipLaunchKernelGGL(k_round_end, dim3(1, ng), dim3(BLOCK), 0, st, g, R, 1);
     if (R.node_acc) hipLaunchKernelGGL(k_node_acc<W>, dim3(list_grid(g), ng), dim3(BLOCK), 0, st, g, R);
