@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "pp.h"
+#include "pp_close.h"
 
 namespace pp {
 
@@ -119,7 +120,11 @@ struct Ctrl {
     int32_t exit_round;   // this round, if it pulls, stops each node's list early (0: none)
     int32_t listed;       // the round whose frontier a step's listing has written (0: none)
     int32_t step;         // 1: the step about to close listed a frontier, and no round ran
-    int32_t pad_step;
+    // the round that the closing launch ends, noted by the round's main launch (no
+    // closing launch writes it: see pp_close.h)
+    int32_t close_round;
+    int32_t close_mode;   // its direction, and CLOSE_EXIT
+    int32_t pad_close;
 };
 
 static_assert(sizeof(Ctrl) % 4 == 0, "the control block is staged to the host as 32-bit words");

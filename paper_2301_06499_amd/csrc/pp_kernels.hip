@@ -2727,6 +2727,14 @@ template <int W> __global__ void __launch_bounds__(BLOCK) k_push_commit(GraphDev
     if (R.ctrl->converged || (!init && R.ctrl->mode != MODE_PUSH)) return;
     phase_push_commit<W>(g, R, init, blockIdx.x, gridDim.x);
 }
+// The round that the closing launch will end (see pp_close.h), noted by the first
+// thread of the round's main launch; the start of the round's clock with it.
+PP_DEV void note_round(const GraphDev &g, const RunDev &R, Ctrl *C, bool start) {
+    const int r = C->round;
+    if (start && r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
+    C->close_round = r;
+    C->close_mode = C->mode | (exits(g, C, r) ? CLOSE_EXIT : 0);
+}
 // The pull, or in a push round that follows a pull the frontier listing (the
 // push's first phase, in the same launch slot so that a round takes three
 // launches).  The listing uses at most FRONTIER_BLOCKS blocks: each takes one
@@ -2736,12 +2744,9 @@ template <int W, int KK, bool DEAD = false>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W >= 8 ? 2 : PP_PULL_WAVES)))
 k_pull(GraphDev g, RunDev R0) {
     const RunDev R = group_view(R0, blockIdx.y);
-    const Ctrl *C = R.ctrl;
+    Ctrl *C = R.ctrl;
     if (C->converged) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the round's start: its first launch's first block
-        const int r = C->round;
-        if (r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) note_round(g, R, C, true);
     if (C->mode == MODE_PULL) {
         if (exits(g, C, C->round)) {
             const int nb = exit_blocks(gridDim.x, W);
@@ -2758,12 +2763,9 @@ template <int W>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(PP_PULL_SHORT_WAVES)))
 k_pull_short(GraphDev g, RunDev R0) {
     const RunDev R = group_view(R0, blockIdx.y);
-    const Ctrl *C = R.ctrl;
+    Ctrl *C = R.ctrl;
     if (C->converged) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the round's start: its first launch's first block
-        const int r = C->round;
-        if (r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) note_round(g, R, C, true);
     if (C->mode == MODE_PULL) {
         phase_pull_lists<W>(g, R, blockIdx.x, gridDim.x);
     } else if (C->prev_mode == MODE_PULL && C->listed != C->round && blockIdx.x < FRONTIER_BLOCKS) {
@@ -2793,8 +2795,7 @@ k_step(GraphDev g, RunDev R0, int push_blocks) {
     const bool pull = C->mode == MODE_PULL, after_pull = C->prev_mode == MODE_PULL, listed = C->listed == r;
     const bool list = !pull && after_pull && !listed;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        // the round's start: its first launch's first block
-        if ((pull || !after_pull || list) && r < R.cap) R.phase_log[(int64_t)r * 3] = (int64_t)wall_clock64();
+        note_round(g, R, C, pull || !after_pull || list);
         C->step = list ? 1 : 0;   // read by the closing launch only
     }
     if (pull) {
@@ -2849,16 +2850,6 @@ __global__ void __launch_bounds__(BLOCK) k_seed_init(GraphDev g, RunDev R0, cons
     phase_round_end(g, R, 1, g.pull_grid);
 }
 
-// Blocks of a closing launch of nb blocks that items (words to commit or
-// combine) keep busy: POST_ITEMS per thread, at least one block.  Blocks
-// without items would only add ticket latency, and more than one item per
-// thread adds serial passes of dependent loads; one item measured best.
-constexpr int POST_ITEMS = 1;
-PP_DEV int post_blocks(int64_t items, int nb) {
-    const int64_t b = (items + (int64_t)BLOCK * POST_ITEMS - 1) / ((int64_t)BLOCK * POST_ITEMS);
-    return b < 1 ? 1 : (b < nb ? (int)b : nb);
-}
-
 // Waits until every global memory operation this thread issued has been
 // performed (s_waitcnt with vmcnt 0; expcnt 7 and lgkmcnt 15 leave the other
 // counters alone), with compiler fences so that no memory access moves
@@ -2888,6 +2879,15 @@ PP_DEV bool last_block(int32_t *tickets, int bid, int nb) {
     return true;
 }
 
+// The control block as the closing launch reads it.
+struct CtrlRead {
+    const Ctrl *C;
+    PP_DEV int32_t converged() const { return CTL(C->converged); }
+    PP_DEV int32_t close_round() const { return CTL(C->close_round); }
+    PP_DEV int32_t close_mode() const { return CTL(C->close_mode); }
+    PP_DEV int32_t nodes(int p) const { return CTL(C->lst[p].nodes); }
+};
+
 // The closing launch of a round: the list commit of a push round or the
 // high-degree nodes of a pull round, then the round's end, run by the last
 // block to finish.  Everything the round's end reads from the other blocks
@@ -2906,22 +2906,19 @@ PP_DEV bool last_block(int32_t *tickets, int bid, int nb) {
 template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(GraphDev g, RunDev R0, int steps) {
     const RunDev R = group_view(R0, blockIdx.y);
     Ctrl *C = R.ctrl;
-    if (CTL(C->converged)) {   // set only by the last block, after every block has finished
+    // the blocks this round's items need: the rest leave at once and take no
+    // ticket, so a small round's end does not wait for the whole grid to count off
+    // (a block may get here after the round's end: see pp_close.h)
+    const Closing cl = closing(CtrlRead{C}, g.nhubs, W, (int)gridDim.x, BLOCK);
+    if (cl.nb == 0) {
         if (blockIdx.x == 0 && threadIdx.x == 0) PUT(C->acc_pending, 0);   // no round ran in this slot
         return;
     }
-    const int32_t mode = CTL(C->mode);
-    // the blocks this round's items need (every block reads the same count):
-    // the rest leave at once and take no ticket, so a small round's end does
-    // not wait for the whole grid to count off
-    const int r = CTL(C->round), p = r & 1;
+    const int r = cl.round, mode = cl.mode, nb = cl.nb;
     if (steps && CTL(C->step)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) C->listed = r;
         return;
     }
-    const bool chunked = mode == MODE_PULL && !exits(g, C, r);   // high-degree nodes; else the round's list
-    const int64_t items = (int64_t)(chunked ? g.nhubs : CTL(C->lst[p].nodes)) * W;
-    const int nb = post_blocks(items, (int)gridDim.x);
     if ((int)blockIdx.x >= nb) return;
     // one block alone hands its sums over in LDS and takes no ticket: its round's
     // end reads nothing else of this launch but what the wait below covers
@@ -2931,7 +2928,7 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
     int64_t *const parts = alone ? s_parts : R.post_part;
     const int pstride = alone ? 1 : POST_MAX;
     if (mode == MODE_PULL)
-        phase_pull_hubs<W>(g, R, blockIdx.x, nb, parts, chunked ? g.hub_node : sel(R.f_ids, p), (int)(items / W), pstride);
+        phase_pull_hubs<W>(g, R, blockIdx.x, nb, parts, cl.list ? sel(R.f_ids, r) : g.hub_node, cl.entries, pstride);
     else phase_push_commit<W>(g, R, 0, blockIdx.x, nb, parts, mode == MODE_SPULL, pstride);
     __shared__ int s_last;
     if (!alone || R.G > 1 || g.exit_ok) wait_global_ops();   // its counts and gained bits are atomics in memory
