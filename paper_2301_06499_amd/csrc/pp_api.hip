@@ -657,8 +657,8 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
         };
         if (!(flags & PP_INPUT_ON_DEVICE) && m > 0) {
             if ((rc = dev_alloc(&da, m)) || (rc = dev_alloc(&db, m))) {
+                (void)hipStreamSynchronize(st);   // the uploads above
                 drop_input();
-                (void)hipStreamSynchronize(st);   // the uploads above read host memory
                 free_graph(g);
                 return retry(rc);
             }
@@ -760,12 +760,14 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
                 perm.clear();
             }
         } catch (const std::bad_alloc &) {
+            (void)hipStreamSynchronize(st);   // the uploads above
             free_graph(g);
             return fail(PP_ENOMEM, "host memory for the adjacency build");
         }
         g->m = (int64_t)col.size();
         if ((rc = dev_alloc(&g->rp, n + 1)) || (rc = dev_alloc(&g->trp, n + 1)) || (rc = dev_alloc(&g->col, g->m)) ||
             (rc = dev_alloc(&g->tcol, g->m))) {
+            (void)hipStreamSynchronize(st);
             free_graph(g);
             return rc;
         }

@@ -249,10 +249,18 @@ template <typename T> struct DevBuf {
     }
 };
 
-#define BUILD_TRY(expr)                                                                       \
-    do {                                                                                      \
-        hipError_t e_ = (expr);                                                               \
-        if (e_ != hipSuccess) return set_error(PP_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)); \
+// `code`, once the stream is idle: an early way out gives blocks back (DevBuf)
+// that queued work may still use.
+int drained(hipStream_t st, int code) {
+    (void)hipStreamSynchronize(st);
+    return code;
+}
+
+#define BUILD_TRY(expr)                                                                                    \
+    do {                                                                                                   \
+        hipError_t e_ = (expr);                                                                            \
+        if (e_ != hipSuccess)                                                                              \
+            return drained(st, set_error(PP_EDEVICE, "%s: %s", #expr, hipGetErrorString(e_)));             \
     } while (0)
 
 // keys[0, count) sorted into out (begin..end bits), with temporary storage.
@@ -260,7 +268,7 @@ int sort_keys(uint64_t *in, uint64_t *out, int64_t count, int bits, hipStream_t 
     size_t bytes = 0;
     BUILD_TRY(rocprim::radix_sort_keys(nullptr, bytes, in, out, (size_t)count, 0u, (unsigned)bits, st));
     DevBuf<unsigned char> tmp;
-    if (!tmp.get((int64_t)bytes)) return set_error(PP_ENOMEM, "radix sort storage of %zu bytes", bytes);
+    if (!tmp.get((int64_t)bytes)) return drained(st, set_error(PP_ENOMEM, "radix sort storage of %zu bytes", bytes));
     BUILD_TRY(rocprim::radix_sort_keys(tmp.p, bytes, in, out, (size_t)count, 0u, (unsigned)bits, st));
     BUILD_TRY(hipStreamSynchronize(st));   // the storage goes back after the sort
     return PP_OK;
@@ -270,7 +278,7 @@ int sort_cols(uint32_t *in, uint32_t *out, int64_t count, int bits, hipStream_t 
     size_t bytes = 0;
     BUILD_TRY(rocprim::radix_sort_keys(nullptr, bytes, in, out, (size_t)count, 0u, (unsigned)bits, st));
     DevBuf<unsigned char> tmp;
-    if (!tmp.get((int64_t)bytes)) return set_error(PP_ENOMEM, "radix sort storage of %zu bytes", bytes);
+    if (!tmp.get((int64_t)bytes)) return drained(st, set_error(PP_ENOMEM, "radix sort storage of %zu bytes", bytes));
     BUILD_TRY(rocprim::radix_sort_keys(tmp.p, bytes, in, out, (size_t)count, 0u, (unsigned)bits, st));
     BUILD_TRY(hipStreamSynchronize(st));
     return PP_OK;
@@ -281,7 +289,7 @@ int sort_pairs(uint64_t *k_in, uint64_t *k_out, uint32_t *v_in, uint32_t *v_out,
     size_t bytes = 0;
     BUILD_TRY(rocprim::radix_sort_pairs(nullptr, bytes, k_in, k_out, v_in, v_out, (size_t)count, 0u, 64u, st));
     DevBuf<unsigned char> tmp;
-    if (!tmp.get((int64_t)bytes)) return set_error(PP_ENOMEM, "radix sort storage of %zu bytes", bytes);
+    if (!tmp.get((int64_t)bytes)) return drained(st, set_error(PP_ENOMEM, "radix sort storage of %zu bytes", bytes));
     BUILD_TRY(rocprim::radix_sort_pairs(tmp.p, bytes, k_in, k_out, v_in, v_out, (size_t)count, 0u, 64u, st));
     BUILD_TRY(hipStreamSynchronize(st));
     return PP_OK;
@@ -313,7 +321,7 @@ int device_order(const uint64_t *keys, int64_t count, int64_t n, int shift, cons
     DevBuf<unsigned int> cnt;
     if (!cnt.get(1) || !s0.get(n) || !s1.get(n) || !pd.get(n) || !lab.get(n) || !disc.get(n) || !lev.get(n) ||
         !claim.get(n) || !i0.get(n) || !i1.get(n))
-        return PP_OK;   // the host's searches need no device memory
+        return drained(st, PP_OK);   // the host's searches need no device memory
     auto zero = [&]() { hipLaunchKernelGGL(k_fill_i32z, dim3(1), dim3(BLOCK), 0, st, (int32_t *)cnt.p, (int64_t)1); };
     auto read = [&](unsigned int &c) -> int {
         BUILD_TRY(hipGetLastError());
@@ -345,13 +353,13 @@ int device_order(const uint64_t *keys, int64_t count, int64_t n, int shift, cons
     hipLaunchKernelGGL(k_roots, dim3(grid_for(n)), dim3(BLOCK), 0, st, n, H, lab.p, lev.p, disc.p);
     uint32_t first = (uint32_t)n;   // discovery numbers: roots by id, then the levels' nodes
     for (int L = 0;; ++L) {
-        if (L > ORDER_LEVELS) return PP_OK;
         zero();
         hipLaunchKernelGGL(k_claim, dim3(grid_for(count)), dim3(BLOCK), 0, st, keys, count, shift, mask, L, lab.p, lev.p,
                            disc.p, claim.p);
         hipLaunchKernelGGL(k_claimed, dim3(grid_for(n)), dim3(BLOCK), 0, st, n, lev.p, claim.p, s0.p, i0.p, cnt.p);
         if ((rc = read(c))) return rc;
         if (c == 0) break;
+        if (L == ORDER_LEVELS) return PP_OK;   // the stream is idle here: read() has waited
         if ((rc = sort_pairs(s0.p, s1.p, i0.p, i1.p, c, st))) return rc == PP_ENOMEM ? PP_OK : rc;
         hipLaunchKernelGGL(k_found, dim3(grid_for(c)), dim3(BLOCK), 0, st, i1.p, c, L + 1, first, lev.p, disc.p);
         first += c;
@@ -375,7 +383,7 @@ int keys_to_rows(const uint64_t *keys, int64_t count, int64_t n, int shift, DevR
     DevBuf<int64_t> rp;
     DevBuf<int32_t> col;
     if (!len.get(n + 1) || !rp.get(n + 1) || !col.get(count))
-        return set_error(PP_ENOMEM, "device rows of %lld nodes and %lld arcs", (long long)n, (long long)count);
+        return drained(st, set_error(PP_ENOMEM, "device rows of %lld nodes and %lld arcs", (long long)n, (long long)count));
     hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(n + 1)), dim3(BLOCK), 0, st, len.p, n + 1);
     if (count > 0) {
         hipLaunchKernelGGL(k_row_lengths, dim3(grid_for(count)), dim3(BLOCK), 0, st, keys, count, shift, len.p);
@@ -387,7 +395,7 @@ int keys_to_rows(const uint64_t *keys, int64_t count, int64_t n, int shift, DevR
     const int64_t *lin = reinterpret_cast<const int64_t *>(len.p);
     BUILD_TRY(rocprim::exclusive_scan(nullptr, bytes, lin, rp.p, (int64_t)0, (size_t)(n + 1), rocprim::plus<int64_t>(), st));
     DevBuf<unsigned char> tmp;
-    if (!tmp.get((int64_t)bytes)) return set_error(PP_ENOMEM, "scan storage of %zu bytes", bytes);
+    if (!tmp.get((int64_t)bytes)) return drained(st, set_error(PP_ENOMEM, "scan storage of %zu bytes", bytes));
     BUILD_TRY(rocprim::exclusive_scan(tmp.p, bytes, lin, rp.p, (int64_t)0, (size_t)(n + 1), rocprim::plus<int64_t>(), st));
     BUILD_TRY(hipStreamSynchronize(st));
     out.rp = rp.release();
@@ -403,7 +411,7 @@ int device_check_arcs(const int32_t *a, const int32_t *b, int64_t m, int64_t n, 
     *first_bad = -1;
     if (m <= 0) return PP_OK;
     DevBuf<unsigned long long> flag;
-    if (!flag.get(1)) return set_error(PP_ENOMEM, "a flag");
+    if (!flag.get(1)) return drained(st, set_error(PP_ENOMEM, "a flag"));
     const unsigned long long none = ~0ull;
     BUILD_TRY(hipMemcpyAsync(flag.p, &none, sizeof(none), hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_check_arcs, dim3(grid_for(m)), dim3(BLOCK), 0, st, a, b, m, n, node_graph, flag.p);
@@ -427,7 +435,7 @@ int device_build(int64_t n, int64_t m, const int32_t *a, const int32_t *b, bool 
                          (long long)slots);
     // sorted keys without self-loops and duplicates
     DevBuf<uint64_t> k0, k1;
-    if (!k0.get(slots) || !k1.get(slots)) return set_error(PP_ENOMEM, "%lld arc keys", (long long)slots);
+    if (!k0.get(slots) || !k1.get(slots)) return drained(st, set_error(PP_ENOMEM, "%lld arc keys", (long long)slots));
     int64_t count = 0;
     if (m > 0) {
         hipLaunchKernelGGL(k_arc_keys, dim3(grid_for(m)), dim3(BLOCK), 0, st, a, b, m, shift, undirected, no_arc,
@@ -436,11 +444,11 @@ int device_build(int64_t n, int64_t m, const int32_t *a, const int32_t *b, bool 
         int rc = sort_keys(k0.p, k1.p, slots, bits, st);
         if (rc) return rc;
         DevBuf<unsigned int> ucount;
-        if (!ucount.get(1)) return set_error(PP_ENOMEM, "a count");
+        if (!ucount.get(1)) return drained(st, set_error(PP_ENOMEM, "a count"));
         size_t bytes = 0;
         BUILD_TRY(rocprim::unique(nullptr, bytes, k1.p, k0.p, ucount.p, (size_t)slots, rocprim::equal_to<uint64_t>(), st));
         DevBuf<unsigned char> tmp;
-        if (!tmp.get((int64_t)bytes)) return set_error(PP_ENOMEM, "unique storage of %zu bytes", bytes);
+        if (!tmp.get((int64_t)bytes)) return drained(st, set_error(PP_ENOMEM, "unique storage of %zu bytes", bytes));
         BUILD_TRY(rocprim::unique(tmp.p, bytes, k1.p, k0.p, ucount.p, (size_t)slots, rocprim::equal_to<uint64_t>(), st));
         unsigned int u = 0;
         BUILD_TRY(hipMemcpyAsync(&u, ucount.p, sizeof(u), hipMemcpyDeviceToHost, st));
@@ -465,7 +473,7 @@ int device_build(int64_t n, int64_t m, const int32_t *a, const int32_t *b, bool 
         rp0.p = r0.rp;
         col0.p = r0.col;
         DevBuf<int32_t> indeg;
-        if (!indeg.get(n)) return set_error(PP_ENOMEM, "in-degrees of %lld nodes", (long long)n);
+        if (!indeg.get(n)) return drained(st, set_error(PP_ENOMEM, "in-degrees of %lld nodes", (long long)n));
         hipLaunchKernelGGL(k_fill_i32z, dim3(grid_for(n)), dim3(BLOCK), 0, st, indeg.p, n);
         if (count > 0) {
             // the columns alone, sorted, in the key buffer free now: an atomic per
@@ -519,7 +527,7 @@ int device_build(int64_t n, int64_t m, const int32_t *a, const int32_t *b, bool 
     }
     if (!perm.empty()) {
         if (!perm_d.p) {
-            if (!perm_d.get(n)) return set_error(PP_ENOMEM, "the storage order");
+            if (!perm_d.get(n)) return drained(st, set_error(PP_ENOMEM, "the storage order"));
             BUILD_TRY(hipMemcpyAsync(perm_d.p, perm.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st));
         }
         // rows in storage order: relabel, sort

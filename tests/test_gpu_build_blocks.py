@@ -1,0 +1,105 @@
+"""Blocks of a graph build go back to the caller's allocator only when nothing
+queued on the build's stream can still use them: on success, where the device
+gives up finding the storage order, and where any one allocation fails."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from hipmem import DeviceArray, hip
+from paper_2301_06499_amd import inputs as gen
+from paper_2301_06499_amd import pp
+
+pytestmark = pytest.mark.gpu
+
+NOT_READY = 600   # hipErrorNotReady
+
+
+class Watch:
+    """Fails allocation `fail_at` (none when negative) and notes every block that
+    comes back while its stream still has work queued; nothing is freed before
+    the end, so a write to such a block meets memory of its own."""
+
+    def __init__(self, fail_at=-1):
+        self.fail_at, self.allocs, self.live, self.blocks, self.early = fail_at, 0, set(), [], 0
+
+    def alloc(self, n, stream):
+        self.allocs += 1
+        if self.allocs - 1 == self.fail_at:
+            return 0
+        p = ctypes.c_void_p()
+        assert hip().hipMalloc(ctypes.byref(p), n) == 0
+        self.blocks.append(p)
+        self.live.add(p.value)
+        return p.value
+
+    def release(self, p, stream):
+        self.early += hip().hipStreamQuery(ctypes.c_void_p(stream)) == NOT_READY
+        self.live.remove(p)
+
+    def close(self):
+        assert hip().hipDeviceSynchronize() == 0
+        for p in self.blocks:
+            hip().hipFree(p)
+
+
+def build(watch, stream, *args, **kw):
+    pp.pp_set_allocator(watch.alloc, watch.release)
+    try:
+        pp.pp_csr_build(*args, stream=stream, **kw).free()
+        return pp.PP_OK
+    except pp.PPError as e:
+        return e.code
+    finally:
+        pp.pp_set_allocator(None, None)
+
+
+@pytest.fixture
+def stream():
+    st = ctypes.c_void_p()
+    assert hip().hipStreamCreateWithFlags(ctypes.byref(st), 1) == 0
+    yield st.value
+    hip().hipStreamDestroy(st)
+
+
+def test_a_search_too_deep_for_the_device(stream):
+    """64 layers of 16 nodes behind the node with the most predecessors, and a wide
+    level after them.  Each node takes arcs from four of the layer before, and the
+    ids are shuffled among those of many short lists, so that a pass over the arcs
+    in order carries a label through several layers."""
+    layers, w, leaves, fill = 64, 16, 100_000, 1_000_000
+    rng = np.random.default_rng(5)
+    hub, first = 0, 1
+    layer = first + np.arange(layers * w).reshape(layers, w)
+    leaf = layer[-1, -1] + 1 + np.arange(leaves)
+    tail = leaf[-1] + 1 + np.arange(fill)       # sources of the short lists
+    pool = tail[-1] + 1 + np.arange(fill)       # their heads, all found by the first search
+    src = [np.full(w, hub), np.repeat(layer[:-1], 4), np.full(leaves, layer[-1, 0]), np.repeat(tail, 6), tail[:300],
+           np.full(fill, hub)]
+    dst = [layer[0], ((np.arange(w)[:, None] + np.arange(4)) % w + layer[1:, :1, None]).reshape(-1), leaf,
+           rng.choice(pool, 6 * fill), np.full(300, hub), pool]
+    mix = rng.permutation(pool[-1] + 1).astype(np.int32)
+    watch = Watch()
+    assert build(watch, stream, len(mix), mix[np.concatenate(src)], mix[np.concatenate(dst)], build="device") == pp.PP_OK
+    assert watch.live == set() and watch.early == 0
+    watch.close()
+
+
+@pytest.mark.parametrize("kw,device", [({}, False), ({}, True), ({"build": "device"}, True),
+                                                ({"undirected": True, "build": "device"}, False),
+                                                ({"keep_order": True, "build": "device"}, False)])
+def test_each_allocation_failing(stream, kw, device):
+    g = gen.rmat(13, 16, 3)
+    src, dst = (DeviceArray(g.src), DeviceArray(g.dst)) if device else (g.src, g.dst)
+    k, code = 0, None
+    while True:
+        w = Watch(k)
+        print("build", kw, "device" if device else "host", "failing allocation", k, flush=True)
+        code = build(w, stream, g.n, src, dst, **kw)
+        assert code in (pp.PP_OK, pp.PP_ENOMEM), code
+        assert w.live == set() and w.early == 0
+        w.close()
+        if w.allocs <= k:   # nothing failed
+            break
+        k += 1
+    assert code == pp.PP_OK and k > 10
