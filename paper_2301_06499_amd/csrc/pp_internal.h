@@ -6,6 +6,7 @@
 
 #include "pp.h"
 #include "pp_close.h"
+#include "pp_light.h"
 
 namespace pp {
 

@@ -113,11 +113,11 @@ template <typename T> PP_DEV T wave_sum(T v) {
     return v;
 }
 
-PP_DEV int wave_inclusive_scan(int v) {
+template <typename T> PP_DEV T wave_inclusive_scan(T v) {
     const int ln = lane_id();
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(v, o);
+        const T t = __shfl_up(v, o);
         if (ln >= o) v += t;
     }
     return v;
@@ -2482,12 +2482,11 @@ PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool
     // entry `slot` (slot < 0: none) of the list of parity q: node id with deg
     // arcs from beg on; the whole wave calls
     auto place = [&](int slot, int32_t id, int64_t beg, int deg, int q) {
-        const int incl = wave_inclusive_scan(deg);
+        const uint32_t incl = wave_inclusive_scan((uint32_t)deg);
         unsigned long long base = 0;
-        if (ln == 63) base = atomicAdd(&s_arcs[q], (unsigned long long)(uint32_t)incl);
+        if (ln == 63) base = atomicAdd(&s_arcs[q], (unsigned long long)incl);
         base = __shfl(base, 63);
-        const int64_t at = (int64_t)base + incl - deg;
-        const int start = at < H ? (int)at : H;
+        const int start = light_start(base, incl, (uint32_t)deg, H);
         if (slot >= 0) {
             s_beg[slot] = (uint32_t)beg;
             s_start[slot] = start;
