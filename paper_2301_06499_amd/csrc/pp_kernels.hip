@@ -2455,7 +2455,7 @@ PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool
     __shared__ unsigned long long s_val[H * W];
     __shared__ uint16_t s_map[H];             // frontier entry of each arc
     __shared__ uint16_t s_slot[H];            // table slots in use, in order of insertion
-    __shared__ uint32_t s_beg[LC];            // first predecessor arc
+    __shared__ uint32_t s_beg[LC];            // first predecessor arc (from the view's first)
     __shared__ int32_t s_start[LC], s_id[LC]; // first flat arc; node
     __shared__ unsigned long long s_del[LC * W];
     // by parity of the round: new bits, nodes that gained them, their predecessor arcs
@@ -2470,6 +2470,7 @@ PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool
     int64_t reached = CTL(C->reached), last = CTL(C->last_count);
     int64_t prev_arcs = CTL(C->f_arcs[(r - 1) & 1]);
     const int n0 = CTL(C->lst[(r - 1) & 1].nodes);
+    const int64_t first_arc = g.trp[g.n0];   // 0 but for a graph of a batch
     for (int i = tid; i < H; i += NT) s_key[i] = -1;
     for (int i = tid; i < H * W; i += NT) s_val[i] = 0;
     if (tid < 2) {
@@ -2488,7 +2489,7 @@ PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool
         base = __shfl(base, 63);
         const int start = light_start(base, incl, (uint32_t)deg, H);
         if (slot >= 0) {
-            s_beg[slot] = (uint32_t)beg;
+            s_beg[slot] = light_offset(beg, first_arc);
             s_start[slot] = start;
             s_id[slot] = id;
             if (deg <= PUSH_LIGHT)
@@ -2538,7 +2539,7 @@ PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool
                 d[u] = 0;
                 if (arc < A) {
                     const int en = s_map[arc];
-                    v[u] = g.tcol[s_beg[en] + (uint32_t)(arc - s_start[en])];
+                    v[u] = g.tcol[light_arc(first_arc, s_beg[en], arc, s_start[en])];
                     d[u] = s_del[en * W + w];
                 }
             }

@@ -18,4 +18,12 @@ PP_HD int light_start(uint64_t base, uint32_t incl, uint32_t deg, int H) {
     return at < (uint64_t)H ? (int)at : H;
 }
 
+// First predecessor arc of a node as the frontier in LDS keeps it: from the
+// view's first arc, since a batch may hold 2^32 arcs and more where each of its
+// graphs holds fewer.
+PP_HD uint32_t light_offset(int64_t beg, int64_t view_first) { return (uint32_t)(beg - view_first); }
+PP_HD int64_t light_arc(int64_t view_first, uint32_t offset, int32_t arc, int32_t start) {
+    return view_first + offset + (arc - start);
+}
+
 }  // namespace pp

@@ -1,6 +1,6 @@
 """The light rounds' index arithmetic (pp_light.h, compiled for the host) where
 32 bits run out: a wave of frontier entries whose predecessor lists hold 2^31
-arcs and more together."""
+arcs and more together, and a small graph behind 2^32 arcs of a batch."""
 import os
 import shutil
 import subprocess
@@ -50,6 +50,23 @@ int main() {
             wrong += base != at;
         }
     }
+    printf("%d wrong\n", wrong);
+    return wrong != 0;
+}
+""")
+
+
+def test_arcs_of_a_graph_far_into_a_batch(tmp_path):
+    run(tmp_path, r"""
+#include <initializer_list>
+#include <stdio.h>
+#include "pp_light.h"
+int main() {
+    int wrong = 0;
+    for (int64_t first : {(int64_t)0, (int64_t)1 << 31, ((int64_t)1 << 32) - 3, (int64_t)1 << 32, (int64_t)5000000000})
+        for (int64_t at : {(int64_t)0, (int64_t)7, ((int64_t)1 << 32) - 20})
+            for (int arc : {100, 103, 115})
+                wrong += pp::light_arc(first, pp::light_offset(first + at, first), arc, 100) != first + at + (arc - 100);
     printf("%d wrong\n", wrong);
     return wrong != 0;
 }
