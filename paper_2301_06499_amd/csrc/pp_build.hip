@@ -71,6 +71,12 @@ __global__ void __launch_bounds__(BLOCK) k_col_counts(const uint32_t *cols, int6
     }
 }
 
+// The same of columns in any order, where there is no memory to sort them.
+__global__ void __launch_bounds__(BLOCK) k_col_adds(const uint32_t *cols, int64_t count, int32_t *cnt) {
+    for (int64_t i = blockIdx.x * (int64_t)BLOCK + threadIdx.x; i < count; i += (int64_t)gridDim.x * BLOCK)
+        atomicAdd(&cnt[cols[i]], 1);
+}
+
 // ---- the storage order on the device (device_order below)
 
 // Nodes with in-degree at least thr: sort key (in-degree descending, id).
@@ -335,7 +341,7 @@ int device_order(const uint64_t *keys, int64_t count, int64_t n, int shift, cons
     hipLaunchKernelGGL(k_hot_keys, dim3(grid_for(n)), dim3(BLOCK), 0, st, indeg, n, thr, s0.p, cnt.p);
     if ((rc = read(H))) return rc;
     if (H == 0) return PP_OK;   // lattices, paths: many levels
-    if ((rc = sort_keys(s0.p, s1.p, H, 64, st))) return rc;
+    if ((rc = sort_keys(s0.p, s1.p, H, 64, st))) return rc == PP_ENOMEM ? PP_OK : rc;
     hipLaunchKernelGGL(k_order_init, dim3(grid_for(n)), dim3(BLOCK), 0, st, n, H, lab.p, lev.p, claim.p);
     hipLaunchKernelGGL(k_hot_init, dim3(grid_for(H)), dim3(BLOCK), 0, st, s1.p, H, lab.p, lev.p, disc.p, pd.p);
     for (int pass = 1;; ++pass) {
@@ -483,8 +489,10 @@ int device_build(int64_t n, int64_t m, const int32_t *a, const int32_t *b, bool 
             hipLaunchKernelGGL(k_key_cols, dim3(grid_for(count)), dim3(BLOCK), 0, st, k0.p, count, mask,
                                reinterpret_cast<int32_t *>(c0));
             BUILD_TRY(hipGetLastError());
-            if ((rc = sort_cols(c0, c1, count, shift, st))) return rc;
-            hipLaunchKernelGGL(k_col_counts, dim3(grid_for(count)), dim3(BLOCK), 0, st, c1, count, indeg.p);
+            rc = sort_cols(c0, c1, count, shift, st);
+            if (rc && rc != PP_ENOMEM) return rc;
+            if (rc) hipLaunchKernelGGL(k_col_adds, dim3(grid_for(count)), dim3(BLOCK), 0, st, c0, count, indeg.p);
+            else hipLaunchKernelGGL(k_col_counts, dim3(grid_for(count)), dim3(BLOCK), 0, st, c1, count, indeg.p);
         }
         BUILD_TRY(hipGetLastError());
         bool moved = false, done = false;

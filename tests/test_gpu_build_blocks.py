@@ -21,10 +21,11 @@ class Watch:
     the end, so a write to such a block meets memory of its own."""
 
     def __init__(self, fail_at=-1):
-        self.fail_at, self.allocs, self.live, self.blocks, self.early = fail_at, 0, set(), [], 0
+        self.fail_at, self.allocs, self.live, self.blocks, self.early, self.sizes = fail_at, 0, set(), [], 0, []
 
     def alloc(self, n, stream):
         self.allocs += 1
+        self.sizes.append(n)
         if self.allocs - 1 == self.fail_at:
             return 0
         p = ctypes.c_void_p()
@@ -103,3 +104,24 @@ def test_each_allocation_failing(stream, kw, device):
             break
         k += 1
     assert code == pp.PP_OK and k > 10
+
+
+def test_no_memory_for_the_order_on_the_device(stream):
+    """Without memory to sort the columns, or for any part of the device's search
+    for the storage order, the build does without it and gives the same arrays."""
+    g = gen.rmat(13, 16, 3)
+    w = Watch()
+    assert build(w, stream, g.n, g.src, g.dst, build="device") == pp.PP_OK
+    w.close()
+    want = pp.pp_graph_get_csr(pp.pp_csr_build(g.n, g.src, g.dst, build="device"))
+    order = [4] + [k * g.n for k in (8, 8, 4, 4, 4, 4, 8, 4, 4)]   # a counter and the search's nine arrays
+    i = next(i for i in range(len(w.sizes)) if w.sizes[i:i + len(order)] == order)
+    for k in range(i - 1, i + len(order) + 2):   # the columns' sort before them, two sorts after them
+        f = Watch(k)
+        pp.pp_set_allocator(f.alloc, f.release)
+        try:
+            got = pp.pp_graph_get_csr(pp.pp_csr_build(g.n, g.src, g.dst, build="device", stream=stream))
+        finally:
+            pp.pp_set_allocator(None, None)
+        assert all(np.array_equal(a, b) for a, b in zip(want, got)), k
+        f.close()
