@@ -690,8 +690,12 @@ extern "C" int pp_csr_build(int64_t n, int64_t m, const int32_t *src, const int3
         }
         pp::DevRows rows, trows;
         if (tr) std::swap(a, b);
-        rc = pp::device_build(n, m, a, b, und, order, G == 1 && !(flags & (PP_KEEP_ORDER | PP_HUBS_ONLY)), rows, trows,
-                              perm, st);
+        try {
+            rc = pp::device_build(n, m, a, b, und, order, G == 1 && !(flags & (PP_KEEP_ORDER | PP_HUBS_ONLY)), rows,
+                                  trows, perm, st);
+        } catch (const std::bad_alloc &) {
+            rc = fail(PP_ENOMEM, "host memory for the storage order");
+        }
         drop_input();   // device_build has synchronised the stream
         g->rp = rows.rp;
         g->col = rows.col;

@@ -26,7 +26,8 @@ int device_check_arcs(const int32_t *a, const int32_t *b, int64_t m, int64_t n, 
 // may fill perm (the stored id of each input node) and return true; the rows
 // are then stored in that order (perm is cleared when it returns false).
 // searches: the order is one graph's, with the breadth-first numbering, and may
-// be found on the device instead.
+// be found on the device instead.  Throws std::bad_alloc, with the stream idle,
+// where the host has no memory for its part.
 using OrderFn = std::function<bool(const std::vector<int64_t> &, const std::vector<int64_t> &,
                                    const std::function<const int32_t *()> &, std::vector<int32_t> &)>;
 int device_build(int64_t n, int64_t m, const int32_t *a, const int32_t *b, bool undirected, const OrderFn &order,

@@ -373,9 +373,9 @@ int device_order(const uint64_t *keys, int64_t count, int64_t n, int shift, cons
     hipLaunchKernelGGL(k_final_keys, dim3(grid_for(n)), dim3(BLOCK), 0, st, n, lab.p, disc.p, s0.p, i0.p);
     BUILD_TRY(hipGetLastError());
     if ((rc = sort_pairs(s0.p, s1.p, i0.p, i1.p, n, st))) return rc == PP_ENOMEM ? PP_OK : rc;
+    perm.resize((size_t)n);   // (may throw: the stream is idle)
     hipLaunchKernelGGL(k_final_perm, dim3(grid_for(n - H)), dim3(BLOCK), 0, st, i1.p, n - (int64_t)H, H, pd.p);
     BUILD_TRY(hipGetLastError());
-    perm.resize((size_t)n);
     BUILD_TRY(hipMemcpyAsync(perm.data(), pd.p, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, st));
     BUILD_TRY(hipStreamSynchronize(st));
     perm_d.p = pd.release();
@@ -506,6 +506,7 @@ int device_build(int64_t n, int64_t m, const int32_t *a, const int32_t *b, bool 
         std::vector<int64_t> rp_h, trp_h;
         std::vector<int32_t> deg_h;
         if (!done) {
+            BUILD_TRY(hipStreamSynchronize(st));   // the vectors may throw
             rp_h.resize((size_t)n + 1);
             trp_h.assign((size_t)n + 1, 0);
             deg_h.resize((size_t)n);
