@@ -2492,7 +2492,7 @@ int propagate_s_rows(pp_graph g, const int32_t *seeds, int32_t s, void *region, 
     bool overflow = false;
     const GraphDev gv = graph_view(g, nullptr, 0);
     std::vector<int32_t> hs((size_t)kb);
-    std::vector<int64_t> hc((size_t)cap_rounds, 0);
+    std::vector<int64_t> hc;   // finds of the passes run
     hipError_t e = hipSuccess;
     for (int first = 0; first < s && e == hipSuccess; first += kb) {
         const int kk = std::min(kb, s - first);
@@ -2514,6 +2514,7 @@ int propagate_s_rows(pp_graph g, const int32_t *seeds, int32_t s, void *region, 
             for (int r = last + 1; r <= upto && e == hipSuccess; ++r)
                 e = pp::launch_seq_rows(gv, S, g->seq_heavy, g->nseq_heavy, g->nseq_giant, r, st);
             last = upto;
+            if (hc.size() <= (size_t)last) hc.resize((size_t)last + 1);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(hc.data() + read, S.sum_cnt + read, sizeof(int64_t) * (size_t)(last + 1 - read),
                                    hipMemcpyDeviceToHost, st);
