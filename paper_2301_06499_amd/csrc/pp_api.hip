@@ -1919,6 +1919,7 @@ extern "C" int pp_run_snapshot(pp_run r, pp_run *copy) {
     }
     int rc = alloc_run_dev(r->g, c->dev, r->s, r->k, r->sg, r->W, r->cap, r->dev.seed_counts != nullptr,
                            std::max(pp::pull_grid_for(ts->ntiles, r->W), r->pgrid));
+    if (!rc) rc = dev_alloc(&c->dseeds, (int64_t)c->G * c->s);   // a reset of the copy places its seeds there
     if (!rc && c->grouped && (rc = dev_alloc(&c->iseeds, (int64_t)c->G * c->s)) == PP_OK &&
         (rc = dev_alloc(&c->dpos, (int64_t)c->G * c->s)) == PP_OK)
         rc = dev_alloc(&c->dcur, c->k);
