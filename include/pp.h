@@ -507,8 +507,11 @@ int pp_progressive_sample(pp_graph g, const int32_t *pool, int32_t pool_len, int
  *              signatures plus cap_rounds x 8 bytes of counts, allocated
  *              here and freed before return (the graph keeps a list of its
  *              nodes with long successor lists from the first call on).
- *              From eight on, the seeds run 8, 16, 32, ... 512 at a time (the
- *              most that is at most this many), in the same memory.
+ *              From eight on, the seeds run 8, 16, 32, ... 512 at a time: the
+ *              most that is at most this many, in the same memory; or, with 0
+ *              and where 4 MiB hold them, the least that is at least this many,
+ *              in at most twice that memory (if it is there).  (More than 512
+ *              on a tiny graph run at once.)
  *   stream     hipStream_t or NULL (the graph's stream); synchronous.
  *   counts     host [cap_rounds], zeroed first: counts[r] = pairs (u, x_i)
  *              with d(u, x_i) = r, counts[0] = s.

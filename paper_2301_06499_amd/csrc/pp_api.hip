@@ -2341,18 +2341,9 @@ extern "C" int pp_progressive_sample(pp_graph g, const int32_t *pool, int32_t po
 // first pass without a find; the host checks every 8 passes.
 namespace {
 
-// One device region holds every buffer of a PROPAGATE-S call for k seeds in
-// flight over ceil(n/64) words and a pass log of cap entries (each part
-// 256-byte aligned): both signatures of every seed, per-seed pass counts,
-// the pass log, per-seed arcs examined, states, last passes, the count of
-// running seeds, and the device copy of the batch's seed ids.
-int64_t seq_region_bytes(int64_t k, int64_t nw, int64_t cap) {
-    auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };
-    return up(16 * k * nw) + up(8 * k) + up(8 * cap) + up(8 * k) + up(4 * k) + up(4 * k) + up(4) + up(4 * k);
-}
-
+// The region of seq_region_bytes.
 void seq_carve(void *base, int64_t k, int64_t nw, int64_t cap, pp::SeqDev &S, int32_t **dseeds) {
-    auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };
+    const auto up = pp::seq_up;
     char *p = (char *)base;
     S.bits = (uint64_t *)p;
     p += up(16 * k * nw);
@@ -2374,20 +2365,9 @@ void seq_carve(void *base, int64_t k, int64_t nw, int64_t cap, pp::SeqDev &S, in
     S.cap = (int32_t)cap;
 }
 
-// Seeds in flight on node-major rows when k were asked for: the most of 8, 16,
-// 32, 64, ... 512 that is at most k, so that the rows (2 n of kb / 8 bytes) fit
-// the memory of k one-bit-per-node signature pairs; 0 below eight.
-int seq_rows_seeds(int64_t k) {
-    int kb = 0;
-    for (int b = 8; b <= 64 * pp::SEQ_WORDS && b <= k; b *= 2) kb = b;
-    return kb;
-}
-
-// The same region laid out for node-major rows of kb seeds (never more than
-// seq_region_bytes of k >= kb seeds: every part is a part of that layout, or no
-// larger than one).
+// The region of seq_rows_bytes.
 void seq_carve_rows(void *base, int64_t n, int kb, int64_t cap, pp::SeqRows &S, int32_t **dseeds) {
-    auto up = [](int64_t b) { return (b + 255) & ~(int64_t)255; };
+    const auto up = pp::seq_up;
     char *p = (char *)base;
     S.row_bytes = kb / 8;
     S.rows = p;
@@ -2543,10 +2523,10 @@ int propagate_s_rows(pp_graph g, const int32_t *seeds, int32_t s, void *region, 
     return PP_OK;
 }
 
-// On the region of k seeds: node-major rows from eight seeds on.
-int propagate_s_in(void *region, int64_t k, pp_graph g, const int32_t *seeds, int32_t s, hipStream_t st,
+// On a region for k seeds at a time: node-major rows of kb seeds, or (kb 0) seed-major.
+int propagate_s_in(void *region, int64_t k, int kb, pp_graph g, const int32_t *seeds, int32_t s, hipStream_t st,
                    int64_t *counts, int32_t cap_rounds, int32_t *D, int64_t *examined) {
-    if (const int kb = seq_rows_seeds(k))
+    if (kb)
         return propagate_s_rows(g, seeds, s, region, kb, st, counts, cap_rounds, D, examined);
     pp::SeqDev S{};
     int32_t *dseeds = nullptr;
@@ -2566,10 +2546,12 @@ extern "C" int pp_propagate_s(pp_graph g, const int32_t *seeds, int32_t s, int32
     hipStream_t st = stream ? (hipStream_t)stream : g->stream;
     pp::AllocStream as(st);
     void *region = nullptr;
-    const int64_t bytes = seq_region_bytes(k, nw, cap_rounds);
-    if ((region = pp::dev_malloc((size_t)bytes)) == nullptr)
+    const int64_t bytes = pp::seq_region_bytes(k, nw, cap_rounds);   // holds the rows of up to k seeds too
+    int kb = pp::seq_rows_seeds(k, g->n, g->m, cap_rounds, concurrent == 0);
+    if (kb > k && (region = pp::dev_malloc((size_t)pp::seq_rows_bytes(g->n, kb, cap_rounds))) == nullptr) kb /= 2;
+    if (!region && (region = pp::dev_malloc((size_t)bytes)) == nullptr)
         return fail(PP_ENOMEM, "PROPAGATE-S: device buffers of %lld bytes", (long long)bytes);
-    rc = propagate_s_in(region, k, g, seeds, s, st, counts, cap_rounds, D, examined);
+    rc = propagate_s_in(region, k, kb, g, seeds, s, st, counts, cap_rounds, D, examined);
     pp::dev_release(region);   // the propagation has synchronised the stream
     return rc;
 }
@@ -2580,28 +2562,30 @@ extern "C" int pp_propagate_s_noalloc(pp_graph g, const int32_t *seeds, int32_t 
     if (rc) return rc;
     const int64_t nw = (g->n + 63) / 64;
     const int64_t most = PP_NOALLOC_BYTES;
-    if (seq_region_bytes(1, nw, cap_rounds) > most)
+    if (pp::seq_region_bytes(1, nw, cap_rounds) > most)
         return fail(PP_EINVAL, "PROPAGATE-S without allocation: one seed over %lld nodes with a log of %d passes "
                                "needs %lld bytes, more than the fixed region's %lld",
-                    (long long)g->n, cap_rounds, (long long)seq_region_bytes(1, nw, cap_rounds), (long long)most);
+                    (long long)g->n, cap_rounds, (long long)pp::seq_region_bytes(1, nw, cap_rounds), (long long)most);
     int64_t k;
     if (concurrent > 0) {
         k = std::min<int64_t>({concurrent, s, 65535});
-        if (seq_region_bytes(k, nw, cap_rounds) > most)
+        if (pp::seq_region_bytes(k, nw, cap_rounds) > most)
             return fail(PP_EINVAL, "PROPAGATE-S without allocation: %lld seeds in flight need %lld bytes, more than "
                                    "the fixed region's %lld",
-                        (long long)k, (long long)seq_region_bytes(k, nw, cap_rounds), (long long)most);
+                        (long long)k, (long long)pp::seq_region_bytes(k, nw, cap_rounds), (long long)most);
     } else {
         // the most seeds in flight, up to min(s, 256), that the region holds
         int64_t lo = 1, hi = std::min<int64_t>(256, s);
         while (lo < hi) {
             const int64_t mid = (lo + hi + 1) / 2;
-            if (seq_region_bytes(mid, nw, cap_rounds) <= most) lo = mid; else hi = mid - 1;
+            if (pp::seq_region_bytes(mid, nw, cap_rounds) <= most) lo = mid; else hi = mid - 1;
         }
         k = lo;
     }
     void *region = nullptr;
     if ((rc = pp::noalloc_region(&region)) != PP_OK) return rc;
     hipStream_t st = stream ? (hipStream_t)stream : g->stream;
-    return propagate_s_in(region, k, g, seeds, s, st, counts, cap_rounds, D, examined);
+    int kb = pp::seq_rows_seeds(k, g->n, g->m, cap_rounds, true);   // the region is there either way
+    if (kb > k && pp::seq_rows_bytes(g->n, kb, cap_rounds) > most) kb /= 2;
+    return propagate_s_in(region, k, kb, g, seeds, s, st, counts, cap_rounds, D, examined);
 }

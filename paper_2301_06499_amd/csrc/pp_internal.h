@@ -7,6 +7,7 @@
 #include "pp.h"
 #include "pp_close.h"
 #include "pp_light.h"
+#include "pp_seq_plan.h"
 
 namespace pp {
 
@@ -357,7 +358,6 @@ struct SeqDev {
 };
 // The same on node-major rows: row_bytes * 8 seeds in flight, a row of bits per
 // node (1, 2, 4 or 8 bytes, or 2, 4 or 8 eight-byte words).
-constexpr int SEQ_WORDS = 8;
 #ifndef PP_SEQ_BLOCKS
 #define PP_SEQ_BLOCKS 2048
 #endif

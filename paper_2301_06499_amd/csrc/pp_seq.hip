@@ -15,7 +15,8 @@
 // the arcs it examined (up to and including the first hit of each node); a
 // seed is done at its first pass that finds nothing.
 //
-// That form serves one to seven seeds in flight.  From eight on the same
+// That form serves one to seven seeds in flight, and more than 512 on a tiny
+// graph (see seq_rows_seeds).  From eight on the same
 // passes run on node-major rows of one bit per seed (k_seq_rows), which walk
 // each node's list once for all of its seeds; below eight a row of a byte
 // would not fit the memory promised (one bit per node, seed and buffer).
