@@ -8,6 +8,7 @@
 #include "pp_close.h"
 #include "pp_light.h"
 #include "pp_seq_plan.h"
+#include "pp_wait.h"
 
 namespace pp {
 

@@ -3012,8 +3012,8 @@ hipError_t launch_redecide(const RunDev &R, int nctrl, int stride, hipStream_t s
 // on the top counter, and the last group advances the generation everyone
 // waits on.  The agent-scope fences publish each block's writes before it
 // arrives and make the others' writes visible after it leaves.  A wait longer
-// than about ten seconds sets `abort`; every later barrier and the round loop
-// then return, so the grid always drains.
+// than about ten seconds (see BoundedWait) sets `abort`; every later barrier and
+// the round loop then return, so the grid always drains.
 PP_DEV bool cluster_barrier(GridBar *b, int bid, int nb) {
     __shared__ int s_abort;
     __syncthreads();
@@ -3035,10 +3035,10 @@ PP_DEV bool cluster_barrier(GridBar *b, int bid, int nb) {
                     atomicAdd(&b->gen, 1u);
                 }
             }
-            const uint64_t t0 = wall_clock64();
+            BoundedWait wait{(uint64_t)wall_clock64(), 0};
             while (CTL(b->gen) == gen) {
                 __builtin_amdgcn_s_sleep(2);
-                if (wall_clock64() - t0 > 1000000000ull) {   // ~10 s at 100 MHz
+                if (wait.expired((uint64_t)wall_clock64())) {
                     atomicExch(&b->abort, 1);
                     break;
                 }
