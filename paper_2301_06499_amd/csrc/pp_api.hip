@@ -1610,7 +1610,7 @@ hipEvent_t slot_event(pp_run r, int i, int which) { return r->timing ? r->ev[(si
 // Whether this run's batches take their rounds as steps of two launches.
 // (groups may then be a round apart: only where no round limit has to stop them together)
 bool by_steps(pp_run r, const GraphDev &gv, bool limited) {
-    return (gv.m < pp::STEP_MAX_ARCS || (gv.short_lists && r->W <= 2)) && !gv.exit_ok && !(limited && r->k > 1) &&
+    return pp::takes_steps(gv.m, gv.short_lists && r->W <= 2, gv.exit_ok, gv.skip_dead) && !(limited && r->k > 1) &&
            !r->timing && !r->dev.node_acc && !r->dev.sparse_pull && r->dev.pull_k != 2;
 }
 

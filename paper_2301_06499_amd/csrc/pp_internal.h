@@ -8,6 +8,7 @@
 #include "pp_close.h"
 #include "pp_light.h"
 #include "pp_seq_plan.h"
+#include "pp_steps.h"
 #include "pp_wait.h"
 
 namespace pp {
@@ -217,13 +218,9 @@ constexpr int EXIT_CHUNK = 256;
 // a pull takes the form from one part in EXIT_SHARE of the (node with
 // successors, live seed) pairs reached on: below, few rows can hold every live
 // bit (R-MAT 18, round 3: 0.04 reached, 0.85 of the arcs would be gathered all
-// the same; round 4: 0.6 reached, 0.11 gathered)
+// the same; round 4: 0.6 reached, 0.11 gathered), and on graphs of EXIT_MIN_ARCS
+// (pp_steps.h) or more
 constexpr int EXIT_SHARE = 8;
-// and on graphs with this many arcs or more: below, a round is bound by its
-// launches and the steps' dependent loads add to it (undirected R-MAT 13,
-// 512 seeds: 3.9 -> 4.5 ms for its 16 groups; ER 10k: 192 -> 204 us; but
-// undirected R-MAT 17, 4M arcs: round 4 96 -> 45 us)
-constexpr int64_t EXIT_MIN_ARCS = (int64_t)1 << 20;
 // after a pull, the heuristic's push becomes another early-exit pull while one
 // node in EXIT_PULL_SHARE or more changed: the push would list all of them (two
 // rows read and a delta written each), the pull reads and writes each row once
@@ -231,14 +228,6 @@ constexpr int64_t EXIT_MIN_ARCS = (int64_t)1 << 20;
 // with eight words and 0.82 ms with four, pull 0.46 and 0.26 ms; the round after
 // that, 0.4% changed, is a push either way; 16 and 64 measure the same)
 constexpr float EXIT_PULL_SHARE = 16;
-// graphs of fewer arcs run their rounds as steps of two launches, as do those
-// whose pulls take the short-list form with any number of arcs: three launches
-// cost 1-3 us more per round (10,000-node graph of 100,000 arcs, 64 seeds: 184
-// -> 174 us; 301^2 lattice 4.80 -> 4.53 ms; 13-scale R-MAT, 512 seeds in two
-// groups: 0.99 -> 0.94 ms; 4096^2 lattice, 60M arcs, 128 seeds: 99.3 -> 96.9).
-// Larger graphs with long lists have their pushes' occupancy to lose (the
-// joint kernel's registers halve it) or early-exit pulls of three launches.
-constexpr int64_t STEP_MAX_ARCS = EXIT_MIN_ARCS;
 // blocks of the launch that take part (half of them with eight-word rows):
 // as many as are resident at once, since each block's start and sums cost more
 // than its share of a late round (R-MAT 24, eight words, the third pull: 1175

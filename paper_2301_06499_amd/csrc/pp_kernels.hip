@@ -2784,7 +2784,7 @@ template <int W> __global__ void __launch_bounds__(BLOCK) k_push(GraphDev g, Run
 // pull, or the push; a push that follows a pull first lists the frontier, in a
 // step of its own.  Such a round is bound by its launches, so one fewer is
 // worth more than the occupancy that the phases' joint registers and LDS cost
-// (STEP_MAX_ARCS has the figures).
+// (takes_steps has the figures).
 template <int W, bool SHORT>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(W >= 8 ? 2 : PP_PULL_WAVES)))
 k_step(GraphDev g, RunDev R0, int push_blocks) {

@@ -1,0 +1,35 @@
+// Which graphs run their rounds as steps of two launches: host code without HIP,
+// so that the tests can check the rule by itself.
+#pragma once
+
+#include <stdint.h>
+
+namespace pp {
+
+// Late pulls stop lists early on graphs with this many arcs or more: below, a
+// round is bound by its launches and the steps' dependent loads add to it
+// (undirected R-MAT 13, 512 seeds: 3.9 -> 4.5 ms for its 16 groups; ER 10k: 192 ->
+// 204 us; but undirected R-MAT 17, 4M arcs: round 4 96 -> 45 us).
+constexpr int64_t EXIT_MIN_ARCS = (int64_t)1 << 20;
+
+// graphs of fewer arcs run their rounds as steps of two launches, as do those
+// whose pulls take the short-list form with any number of arcs: three launches
+// cost 1-3 us more per round (10,000-node graph of 100,000 arcs, 64 seeds: 184
+// -> 174 us; 301^2 lattice 4.80 -> 4.53 ms; 13-scale R-MAT, 512 seeds in two
+// groups: 0.99 -> 0.94 ms; 4096^2 lattice, 60M arcs, 128 seeds: 99.3 -> 96.9).
+// Larger graphs with long lists have their pushes' occupancy to lose (the
+// joint kernel's registers halve it) or early-exit pulls of three launches.
+constexpr int64_t STEP_MAX_ARCS = EXIT_MIN_ARCS;
+
+// short_form: the run's pulls take the short-list form; exit_ok: late pulls may
+// stop lists early; skip_dead: the general pull leaves the rows of nodes without
+// successors alone, a form that the joint kernel does not have, and such graphs
+// have rows beyond the caches to gain from it whatever their arcs (20M nodes, 1M
+// arcs, 64 and 512 seeds: 1.28 and 4.38 ms in three launches, 1.39 and 6.16 in
+// steps; 4M nodes, 512 seeds: 1.95 and 2.27).
+inline bool takes_steps(int64_t m, bool short_form, bool exit_ok, bool skip_dead) {
+    if (exit_ok) return false;
+    return short_form || (m < STEP_MAX_ARCS && !skip_dead);
+}
+
+}  // namespace pp
