@@ -331,6 +331,13 @@ int pp_get_round_log(pp_run r, int32_t *mode, int64_t *arcs, int32_t cap);
  * modes, arcs summed over the groups).  PP_EINVAL for a group outside
  * [0, pp_run_groups). */
 int pp_get_group_log(pp_run r, int32_t group, int32_t *mode, int64_t *arcs, int32_t cap);
+/* How the rounds since the last initialisation ran, which the logs above do not
+ * tell (the outputs are the same every way): counts[0] pulls that stopped each
+ * list early, counts[1] nodes whose rest they left to another launch, counts[2]
+ * push rounds run one after the other in one block, counts[3] frontiers listed in
+ * a step of their own between a pull and a push.  which: the seed group (with the
+ * persistent engine the graph).  Synchronises. */
+int pp_get_path_counts(pp_run r, int32_t which, int64_t counts[4]);
 
 /* With opt.time_kernels: pull_ms[r] = total duration in ms of round r's
  * pull launches (HIP events on the run's stream), summed over every

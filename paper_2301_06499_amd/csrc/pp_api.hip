@@ -1870,6 +1870,20 @@ extern "C" int pp_get_group_log(pp_run r, int32_t group, int32_t *mode, int64_t 
     return PP_OK;
 }
 
+extern "C" int pp_get_path_counts(pp_run r, int32_t which, int64_t *counts) {
+    if (!r || !counts) return fail(PP_EINVAL, "run or counts is NULL");
+    const int nc = r->pgrid ? r->G : r->k;
+    if (which < 0 || which >= nc) return fail(PP_EINVAL, "%d outside [0, %d)", which, nc);
+    const int rc = sync_ctrl(r);
+    if (rc) return rc;
+    const Ctrl &c = r->h_ctrl[(size_t)which * (r->pgrid ? 1 : r->G)];
+    counts[0] = c.exit_pulls;
+    counts[1] = c.exit_left;
+    counts[2] = c.light;
+    counts[3] = c.listings;
+    return PP_OK;
+}
+
 extern "C" int pp_get_round_log(pp_run r, int32_t *mode, int64_t *arcs, int32_t cap) {
     if (!r) return fail(PP_EINVAL, "run is NULL");
     const int rows = std::min(cap, r->cap);

@@ -128,7 +128,11 @@ struct Ctrl {
     // closing launch writes it: see pp_close.h)
     int32_t close_round;
     int32_t close_mode;   // its direction, and CLOSE_EXIT
-    int32_t pad_close;
+    // how the rounds since the initialisation ran (pp_get_path_counts)
+    int32_t exit_pulls;   // pulls that stopped lists early
+    int32_t light;        // light rounds
+    int32_t listings;     // frontiers listed in a step of their own
+    int64_t exit_left;    // nodes that such pulls left to chunks
 };
 
 static_assert(sizeof(Ctrl) % 4 == 0, "the control block is staged to the host as 32-bit words");

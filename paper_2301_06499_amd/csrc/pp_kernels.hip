@@ -2233,8 +2233,9 @@ PP_DEV void phase_round_end(const GraphDev &g, const RunDev &R, int init, int np
     // one reduction for the four sums: pull partials (pull rounds) and the
     // closing launch's partials
     long long v[4] = {0, 0, 0, 0};
+    const bool exited = mode == MODE_PULL && exits(g, C, r);
     if (mode == MODE_PULL) {
-        if (exits(g, C, r)) nparts = exit_blocks(nparts, R.W);
+        if (exited) nparts = exit_blocks(nparts, R.W);
 #pragma unroll 4
         for (int b = threadIdx.x; b < nparts; b += BLOCK) {
             v[0] += R.blk_cnt[b];
@@ -2320,6 +2321,10 @@ PP_DEV void phase_round_end(const GraphDev &g, const RunDev &R, int init, int np
         // the arcs of the nodes changed in this round: a following push's work
         if (mode == MODE_PULL || parts) C->f_arcs[r & 1] = farcs;
         if (mode == MODE_PULL) C->cur ^= 1;
+        if (exited) {
+            C->exit_pulls += 1;
+            C->exit_left += lst_count;
+        }
         C->prev_mode = mode;
         C->hub_cnt = 0;
         C->hub_nodes = 0;
@@ -2466,6 +2471,7 @@ PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool
     const int tid = threadIdx.x, ln = lane_id();
     const int w = tid & (W - 1);
     int r = CTL(C->round);
+    const int r0 = r;
     uint64_t *sig = sel(R.sig, CTL(C->cur));
     int64_t reached = CTL(C->reached), last = CTL(C->last_count);
     int64_t prev_arcs = CTL(C->f_arcs[(r - 1) & 1]);
@@ -2668,6 +2674,7 @@ PP_DEV void light_rounds(const GraphDev &g, const RunDev &R, int max_round, bool
         __syncthreads();
         if (tid == NT - 64) {
             const bool on = cnt && !full;
+            C->light += r - r0 + 1;
             C->acc_pending = 1;
             C->prev_mode = MODE_PUSH;
             C->active = cnt ? 1 : 0;
@@ -2916,7 +2923,10 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
     }
     const int r = cl.round, mode = cl.mode, nb = cl.nb;
     if (steps && CTL(C->step)) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) C->listed = r;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            C->listed = r;
+            C->listings += 1;
+        }
         return;
     }
     if ((int)blockIdx.x >= nb) return;

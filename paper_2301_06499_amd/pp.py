@@ -72,7 +72,7 @@ EXPORTS = ["pp_options_default", "pp_csr_build", "pp_graph_arcs", "pp_graph_node
            "pp_time_round", "pp_mlp_forward", "pp_mlp_loss_grad", "pp_mlp_train", "pp_autotune", "pp_exact_counts",
            "pp_propagate_s", "pp_progressive_sample", "pp_get_node_stats", "pp_set_allocator",
            "pp_propagate_s_noalloc", "pp_run_groups", "pp_run_group_words", "pp_get_group_log",
-           "pp_run_set_plan", "pp_get_round_times"]
+           "pp_run_set_plan", "pp_get_round_times", "pp_get_path_counts"]
 
 MLP_IN, MLP_HID, MLP_OUT = 8, 32, 4
 MLP_PARAMS = MLP_HID * MLP_IN + MLP_HID + MLP_HID * MLP_HID + MLP_HID + MLP_OUT * MLP_HID + MLP_OUT   # 1476
@@ -103,6 +103,7 @@ def lib():
         "pp_run_round": (I32, [P]), "pp_run_words": (I32, [P]),
         "pp_run_groups": (I32, [P]), "pp_run_group_words": (I32, [P]),
         "pp_get_group_log": (ctypes.c_int, [P, I32, P, P, I32]),
+        "pp_get_path_counts": (ctypes.c_int, [P, I32, P]),
         "pp_run_set_plan": (ctypes.c_int, [P, P, I32]),
         "pp_get_round_times": (ctypes.c_int, [P, P, I32]),
         "pp_get_round_log": (ctypes.c_int, [P, P, P, I32]),
@@ -456,6 +457,15 @@ def pp_get_group_log(run: Run, group: int, cap: int):
     arcs = np.zeros(cap, dtype=np.int64)
     _check(lib().pp_get_group_log(run.handle, int(group), _np_ptr(mode), _np_ptr(arcs), int(cap)))
     return mode, arcs
+
+
+def pp_get_path_counts(run: Run, which: int = 0):
+    """How the rounds ran: (pulls that stopped lists early, nodes they left to
+    another launch, push rounds run in one block, frontiers listed in a step of
+    their own) of a seed group, or with the persistent engine of a graph."""
+    counts = np.zeros(4, dtype=np.int64)
+    _check(lib().pp_get_path_counts(run.handle, int(which), _np_ptr(counts)))
+    return tuple(int(c) for c in counts)
 
 
 def pp_run_snapshot(run: Run) -> Run:
