@@ -886,6 +886,7 @@ void free_run_dev(RunDev &d) {
     dev_free(d.feat_log);
     dev_free(d.tickets);
     dev_free(d.post_part);
+    dev_free(d.gain);
     dev_free(d.mlp);
     dev_free(d.plan);
     dev_free(d.node_acc);
@@ -958,7 +959,8 @@ int alloc_run_dev(pp_graph g, RunDev &d, int s_all, int k, int sg, int W, int ca
         (rc = dev_alloc(&d.feat_log, (int64_t)cap * pp::MLP_IN * KG)) || (rc = dev_alloc(&d.mlp, pp::MLP_PARAMS)) ||
         (rc = dev_alloc(&d.plan, cap)) ||
         (rc = dev_alloc(&d.tickets, (int64_t)k * pp::TICKET_INTS)) ||
-        (rc = dev_alloc(&d.post_part, (int64_t)k * 3 * pp::POST_MAX)))
+        (rc = dev_alloc(&d.post_part, (int64_t)k * 3 * pp::POST_MAX)) ||
+        (rc = dev_alloc(&d.gain, (int64_t)k * pp::GAIN_COPIES * pp::GAIN_STRIDE)))
         return rc;
     d.sig[1] = d.sig[0] + n * W;
     d.f_ids[1] = d.f_ids[0] + n;
@@ -1011,6 +1013,7 @@ hipError_t clear_run_dev(pp_graph g, RunDev &d, hipStream_t st, bool with_acc,
         seg(d.feat_log, 4 * cap * pp::MLP_IN * KG, 0u),
         seg(d.ctrl, (int64_t)sizeof(Ctrl) * KG, 0u),
         seg(d.tickets, 4 * pp::TICKET_INTS * k, 0u),
+        seg(d.gain, 8 * pp::GAIN_COPIES * pp::GAIN_STRIDE * k, 0u),
         seg(d.node_acc, d.node_acc ? 8 * n : 0, 0u),
     };
     rows.insert(rows.end(), std::begin(rest), std::end(rest));
@@ -1986,6 +1989,7 @@ extern "C" int pp_run_restore(pp_run r, pp_run from) {
     if (!e) e = cp(b.mlp, a.mlp, sizeof(float) * pp::MLP_PARAMS);
     if (!e) e = cp(b.plan, a.plan, sizeof(int32_t) * cap);
     if (!e) e = cp(b.tickets, a.tickets, sizeof(int32_t) * pp::TICKET_INTS * k);
+    if (!e) e = cp(b.gain, a.gain, sizeof(uint64_t) * pp::GAIN_COPIES * pp::GAIN_STRIDE * k);
     if (!e && b.node_acc && a.node_acc) e = cp(b.node_acc, a.node_acc, sizeof(int64_t) * n);
     if (!e) e = cp(b.ctrl, a.ctrl, sizeof(Ctrl) * KG);
     if (!e) e = cp(b.bar, a.bar, sizeof(pp::GridBar) * KG);

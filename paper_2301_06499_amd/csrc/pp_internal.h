@@ -119,7 +119,6 @@ struct Ctrl {
     int32_t flat;         // bit 0: the sparse round about to run walks its frontier as flattened
                           // arc ranges (read before atomics) rather than direct slots per entry;
                           // bit 1: the fixed threshold's choice (frontier >= PUSH_FILTER_MIN)
-    uint64_t gain[8];     // seed bits that any node gained in the pull round being run
     uint64_t live[8];     // seed bits that any node gained in round exit_round - 1
     int32_t exit_round;   // this round, if it pulls, stops each node's list early (0: none)
     int32_t listed;       // the round whose frontier a step's listing has written (0: none)
@@ -144,6 +143,14 @@ constexpr int TICKET_GROUP = 32;
 constexpr int TICKET_STRIDE = 32;   // int32 per cache line
 constexpr int TICKET_INTS = (TICKET_GROUP + 1) * TICKET_STRIDE;
 constexpr int POST_MAX = 1024;      // blocks of the closing launch at most
+
+// Copies of a pull's gained bits (RunDev::gain), each on a 128-byte line: the
+// blocks of one launch OR into GAIN_COPIES lines instead of one, where their
+// atomics queued for most of the launch's tail (king's-move lattice 700^2, 4M arcs,
+// a dense pull of four words: 45.6 us with one line, 40.7 with 8, 37.2 with 32, 36.0
+// with 64, 33.2 with no gain kept at all; of eight words 73, 68.7, 65.6, 64.4 and 62).
+constexpr int GAIN_COPIES = 64;
+constexpr int GAIN_STRIDE = 16;     // 64-bit words
 
 // Learned cost model: an MLP 8 -> 32 -> 32 -> 4 (ReLU) predicting the log of a
 // round's effective cost under each action: 0 dense pull, 1 push over direct
@@ -280,6 +287,8 @@ struct RunDev {
     float *feat_log;      // [G][cap][8] scheduler features of each round (row 0 unused)
     int32_t *tickets;     // [TICKET_INTS] the closing launch's ticket counters (zero between launches)
     int64_t *post_part;   // [3][POST_MAX] the closing launch's per-block partials
+    uint64_t *gain;       // [GAIN_COPIES][GAIN_STRIDE] seed bits that any node gained in the pull
+                          // round being run (graphs with early-exit pulls), zero between rounds
     GridBar *bar;         // [G] barrier state per cluster
     Ctrl *ctrl;           // [G]: ctrl[0] for the per-round engine, one per graph when clustered
     // scheduler

@@ -97,6 +97,7 @@ PP_DEV RunDev group_view(const RunDev &R0, int grp) {
     R.feat_log = R0.feat_log + grp * G * cap * MLP_IN;
     R.tickets = R0.tickets + (int64_t)grp * TICKET_INTS;
     R.post_part = R0.post_part + (int64_t)grp * 3 * POST_MAX;
+    R.gain = R0.gain + (int64_t)grp * GAIN_COPIES * GAIN_STRIDE;
     R.bar = R0.bar + grp * G;
     R.ctrl = R0.ctrl + grp * G;
     return R;
@@ -850,11 +851,11 @@ PP_DEV void phase_push_commit(const GraphDev &g, const RunDev &R, int init, int 
 
 // ---------------------------------------------------------------- pull
 
-// The seed bits a pull round found new, into the control block's gain: gm is
-// the thread's OR of new bits of word threadIdx.x % W.  Bits only get set, so
-// a block whose bits are all there already (nearly every block but the first
-// few) reads the words and adds nothing.  Every thread of the block calls.
-template <int W> PP_DEV void add_gain(Ctrl *C, uint64_t gm) {
+// The seed bits a pull round found new, into the block's copy of the run's gain:
+// gm is the thread's OR of new bits of word threadIdx.x % W.  Bits only get set,
+// so a block whose bits are all there already reads the words and adds nothing.
+// Every thread of the block calls.
+template <int W> PP_DEV void add_gain(const RunDev &R, int bid, uint64_t gm) {
     __shared__ unsigned long long s_gain[BLOCK / 64][W];
 #pragma unroll
     for (int o = 32; o >= W; o >>= 1) gm |= __shfl_xor(gm, o);
@@ -864,7 +865,8 @@ template <int W> PP_DEV void add_gain(Ctrl *C, uint64_t gm) {
         unsigned long long v = 0;
 #pragma unroll
         for (int k = 0; k < BLOCK / 64; ++k) v |= s_gain[k][threadIdx.x];
-        if (v & ~CTL(C->gain[threadIdx.x])) atomicOr((unsigned long long *)&C->gain[threadIdx.x], v);
+        uint64_t *own = R.gain + (bid & (GAIN_COPIES - 1)) * GAIN_STRIDE + threadIdx.x;
+        if (v & ~CTL(*own)) atomicOr((unsigned long long *)own, v);
     }
 }
 
@@ -1116,7 +1118,7 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
         R.blk_arcs[bid] = (int64_t)ta;
         R.blk_pulled[bid] = (int64_t)tq;
     }
-    if (g.exit_ok) add_gain<W>(C, gm);
+    if (g.exit_ok) add_gain<W>(R, bid, gm);
     if (per_seed && R.G == 1) seed_flush<W>(R, r, sc);
 }
 
@@ -1335,7 +1337,7 @@ PP_DEV void phase_pull_exit(const GraphDev &g, const RunDev &R, int bid, int nb)
         R.blk_arcs[bid] = (int64_t)ta;
         R.blk_pulled[bid] = (int64_t)tq;
     }
-    add_gain<W>(C, gm);
+    add_gain<W>(R, bid, gm);
     if (per_seed) seed_flush<W>(R, r, sc);
 }
 
@@ -1585,7 +1587,7 @@ PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb,
             if (per_seed) seed_bits_keyed<W>(R, r, gi, nw, valid);
         }
     }
-    if (g.exit_ok) add_gain<W>(C, gm);
+    if (g.exit_ok) add_gain<W>(R, bid, gm);
     __shared__ unsigned long long s_red[BLOCK / 64];
     const unsigned long long tp = block_sum<unsigned long long>(pop, s_red);
     const unsigned long long tn = block_sum<unsigned long long>((unsigned long long)nodes, s_red);
@@ -2709,12 +2711,18 @@ PP_DEV void phase_exit_decide(const GraphDev &g, const RunDev &R, int r) {
     Ctrl *C = R.ctrl;
     __syncthreads();   // the round end's stores
     if (threadIdx.x >= 64) return;
-    uint64_t gain = 0;
-    if (threadIdx.x < R.W) {
-        gain = CTL(C->gain[threadIdx.x]);
-        C->live[threadIdx.x] = gain;
-        C->gain[threadIdx.x] = 0;
+    uint64_t gain = 0;   // of word threadIdx.x % W
+#pragma unroll
+    for (int c = 0; c < GAIN_COPIES * 8 / 64; ++c) {
+        const int i = threadIdx.x + c * 64;
+        if (i >= GAIN_COPIES * R.W) break;
+        uint64_t *own = R.gain + i / R.W * GAIN_STRIDE + (i & (R.W - 1));
+        gain |= CTL(*own);
+        *own = 0;
     }
+    for (int o = 32; o >= R.W; o >>= 1) gain |= __shfl_xor(gain, o);
+    if (threadIdx.x < R.W) C->live[threadIdx.x] = gain;
+    else gain = 0;
     const int64_t live = wave_sum((int)__popcll(gain));
     if (threadIdx.x == 0) {
         C->lst[r & 1] = ListCounts{0, 0};   // what an early-exit pull listed
