@@ -851,6 +851,9 @@ PP_DEV void phase_push_commit(const GraphDev &g, const RunDev &R, int init, int 
 
 // ---------------------------------------------------------------- pull
 
+// Whether the pull of round r keeps the bits gained, for the next round to exit early.
+PP_DEV bool keeps_gain(const GraphDev &g, const Ctrl *C, int r) { return g.exit_ok && r >= CTL(C->exit_from); }
+
 // The seed bits a pull round found new, into the block's copy of the run's gain:
 // gm is the thread's OR of new bits of word threadIdx.x % W.  Bits only get set,
 // so a block whose bits are all there already reads the words and adds nothing.
@@ -1118,7 +1121,7 @@ PP_DEV void phase_pull(const GraphDev &g, const RunDev &R, int bid, int nb) {
         R.blk_arcs[bid] = (int64_t)ta;
         R.blk_pulled[bid] = (int64_t)tq;
     }
-    if (g.exit_ok) add_gain<W>(R, bid, gm);
+    if (keeps_gain(g, C, r)) add_gain<W>(R, bid, gm);
     if (per_seed && R.G == 1) seed_flush<W>(R, r, sc);
 }
 
@@ -1224,7 +1227,6 @@ PP_DEV void phase_pull_exit(const GraphDev &g, const RunDev &R, int bid, int nb)
         }
         left_l[ln] = 0;
         wave_lds_fence();
-        pulled += deg;
         int mine = -1;   // the group's node (slot of the list), its next arc and arcs left
         int32_t nd = 0, left = 0, done = 0;
         int64_t a = 0;
@@ -1276,6 +1278,7 @@ PP_DEV void phase_pull_exit(const GraphDev &g, const RunDev &R, int bid, int nb)
 #pragma unroll
                 for (int k = 0; k < P; ++k) row_l[nd * W + sub * P + k] = acc[k];
                 if (more && sub == 0) left_l[nd] = left;
+                if (sub == 0) pulled += more || left < 0 ? done + left : done;   // (the rest will be)
                 mine = -1;
             }
         }
@@ -1587,7 +1590,7 @@ PP_DEV void phase_pull_hubs(const GraphDev &g, const RunDev &R, int bid, int nb,
             if (per_seed) seed_bits_keyed<W>(R, r, gi, nw, valid);
         }
     }
-    if (g.exit_ok) add_gain<W>(R, bid, gm);
+    if (keeps_gain(g, C, r)) add_gain<W>(R, bid, gm);
     __shared__ unsigned long long s_red[BLOCK / 64];
     const unsigned long long tp = block_sum<unsigned long long>(pop, s_red);
     const unsigned long long tn = block_sum<unsigned long long>((unsigned long long)nodes, s_red);
@@ -2319,13 +2322,14 @@ PP_DEV void phase_round_end(const GraphDev &g, const RunDev &R, int init, int np
         if (r < R.cap) R.phase_log[(int64_t)r * 3 + 2] = (int64_t)wall_clock64();   // the round's end
         C->acc_pending = 1;   // a state for the per-node sums
         R.mode_log[r] = (mode == MODE_PUSH && !direct_only && (CTL(C->flat) & 1)) ? MODE_PUSH_FLAT : mode;
-        R.arcs_log[r] = mode == MODE_PULL ? pulled : (mode == MODE_INIT ? 0 : prev_arcs);
+        R.arcs_log[r] = exited ? g.m : (mode == MODE_PULL ? pulled : (mode == MODE_INIT ? 0 : prev_arcs));
         // the arcs of the nodes changed in this round: a following push's work
         if (mode == MODE_PULL || parts) C->f_arcs[r & 1] = farcs;
         if (mode == MODE_PULL) C->cur ^= 1;
         if (exited) {
             C->exit_pulls += 1;
             C->exit_left += lst_count;
+            C->exit_arcs = pulled;
         }
         C->prev_mode = mode;
         C->hub_cnt = 0;
@@ -2706,8 +2710,9 @@ static_assert(LightShape<1, 1024>::LC < PUSH_FILTER_MIN, "light rounds leave fro
 
 // After a pull's round end (round r), by the same block: the bits the pull
 // found new are the next round's live bits, and a pull that follows exits
-// early when enough pairs are reached for single rows to hold them all.
-PP_DEV void phase_exit_decide(const GraphDev &g, const RunDev &R, int r) {
+// early when enough pairs are reached for single rows to hold them all, unless
+// an earlier one (this one: exited) gathered most arcs all the same.
+PP_DEV void phase_exit_decide(const GraphDev &g, const RunDev &R, int r, bool exited) {
     Ctrl *C = R.ctrl;
     __syncthreads();   // the round end's stores
     if (threadIdx.x >= 64) return;
@@ -2726,8 +2731,13 @@ PP_DEV void phase_exit_decide(const GraphDev &g, const RunDev &R, int r) {
     const int64_t live = wave_sum((int)__popcll(gain));
     if (threadIdx.x == 0) {
         C->lst[r & 1] = ListCounts{0, 0};   // what an early-exit pull listed
-        const bool exit = CTL(C->reached) * EXIT_SHARE >= g.open_nodes * live;
+        if (exited && CTL(C->exit_arcs) * EXIT_POOR_DEN > g.m * EXIT_POOR_NUM) C->exit_poor = C->exit_miss;
+        const int64_t reached = CTL(C->reached), pairs = g.open_nodes * live;
+        const float miss = pairs > reached ? (float)(pairs - reached) / (float)pairs : 0.0f;
+        const bool exit = reached * EXIT_SHARE >= pairs && !(C->exit_poor > 0.0f && miss * 2.0f > C->exit_poor);
+        if (exit) C->exit_miss = miss;
         C->exit_round = exit ? r + 1 : 0;
+        C->exit_from = r + 1 + (exit ? 0 : r >> 4);
         // the heuristic's push would first list the pull's changed nodes: with
         // many of them the early-exit pull is the cheaper round (EXIT_PULL_SHARE)
         if (exit && R.sched == PP_SCHED_HEURISTIC && C->feat[0] * EXIT_PULL_SHARE >= 1.0f) C->mode = MODE_PULL;
@@ -2949,7 +2959,8 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
         phase_pull_hubs<W>(g, R, blockIdx.x, nb, parts, cl.list ? sel(R.f_ids, r) : g.hub_node, cl.entries, pstride);
     else phase_push_commit<W>(g, R, 0, blockIdx.x, nb, parts, mode == MODE_SPULL, pstride);
     __shared__ int s_last;
-    if (!alone || R.G > 1 || g.exit_ok) wait_global_ops();   // its counts and gained bits are atomics in memory
+    const bool decides = mode == MODE_PULL && keeps_gain(g, C, r);
+    if (!alone || R.G > 1 || decides) wait_global_ops();   // its counts and gained bits are atomics in memory
     __syncthreads();
     if (!alone) {
         if (threadIdx.x == 0) s_last = last_block(R.tickets, (int)blockIdx.x, nb);
@@ -2957,7 +2968,7 @@ template <int W, bool MLP> __global__ void __launch_bounds__(BLOCK) k_post(Graph
         if (!s_last) return;
     }
     phase_round_end<MLP ? INFER_BLOCK : INFER_NONE>(g, R, 0, g.pull_grid, parts, nb, false, pstride);
-    if (mode == MODE_PULL && g.exit_ok) phase_exit_decide(g, R, r);
+    if (decides) phase_exit_decide(g, R, r, cl.list);
 }
 
 // Per-node sums for reach and distance statistics: after the initialisation
