@@ -1627,7 +1627,7 @@ hipError_t launch_slot(pp_run r, const GraphDev &gv, bool steps, int i) {
 int launch_batch(pp_run r, int k, bool light, bool limited) {
     GraphDev gv = graph_view(r->g, run_tiles(r), r->W);
     const bool steps = by_steps(r, gv, limited);
-    if (!r->opt.use_graph || (r->timing && !r->graph_events) || (light && k == 1)) {
+    if (!r->opt.use_graph || (r->timing && !r->graph_events) || ((light || steps) && k == 1)) {
         if (light) HIP_TRY(noted(r, pp::launch_light(gv, r->dev, r->stream)));
         for (int i = 0; i < k; ++i)
             HIP_TRY(noted(r, launch_slot(r, gv, steps, i)));
@@ -1661,6 +1661,16 @@ int launch_batch(pp_run r, int k, bool light, bool limited) {
     return PP_OK;
 }
 
+// Whether every seed group still running is likely to end in one more step after
+// the first batch (from the control blocks of the last wait).
+bool ends_in_a_step(pp_run r) {
+    for (int j = 0; j < r->k; ++j) {
+        const Ctrl &c = r->h_ctrl[(size_t)j * r->G];
+        if (!c.converged && !pp::one_more_step(c.listings, c.feat[4])) return false;
+    }
+    return true;
+}
+
 // Whether the next round of every seed group still running can be a light one
 // (from the control blocks of the last wait).
 bool light_next(pp_run r) {
@@ -1689,7 +1699,8 @@ extern "C" int pp_propagate_until_converged(pp_run r, int32_t max_rounds, int64_
     // adaptive batches: 8 rounds, then as many as have been launched so far (at
     // most 64) -- a host check costs about as much as a few replayed rounds
     // that find the run converged and return at once
-    int launched = 0;
+    int launched = 0, batches = 0;
+    const bool steps = !r->pgrid && by_steps(r, graph_view(r->g, run_tiles(r), r->W), limit < r->cap - 1);
     // light rounds first where the propagation may run to the log's end and no
     // figures of single launches are asked for (the device checks each round)
     const bool light = limit == r->cap - 1 && G == 1 && !r->timing && !r->dev.node_acc && !r->dev.sparse_pull &&
@@ -1706,6 +1717,7 @@ extern "C" int pp_propagate_until_converged(pp_run r, int32_t max_rounds, int64_
         // round behind them instead of a batch that finds nothing to do (R-MAT 20,
         // nine rounds: 625 -> 588 us per propagation; the 301^2 lattice 5.06 -> 4.77 ms)
         if (light && launched > 0 && r->opt.rounds_per_sync <= 0 && light_next(r)) k = 1;
+        if (steps && batches == 1 && r->opt.rounds_per_sync <= 0 && ends_in_a_step(r)) k = 1;
         // replayed batches come in powers of two so few graphs are captured
         if (r->opt.use_graph) {
             int p = 1;
@@ -1716,6 +1728,7 @@ extern "C" int pp_propagate_until_converged(pp_run r, int32_t max_rounds, int64_
         int rc = launch_batch(r, k, light, limit < r->cap - 1);
         if (rc) return rc;
         launched += k;
+        ++batches;
         if ((rc = sync_state(r, before + k))) return rc;
         if (r->timing) {
             // rounds before..last ran; launches after convergence returned at once

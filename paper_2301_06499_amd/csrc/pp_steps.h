@@ -32,4 +32,14 @@ inline bool takes_steps(int64_t m, bool short_form, bool exit_ok, bool skip_dead
     return short_form || (m < STEP_MAX_ARCS && !skip_dead);
 }
 
+// Whether a single step follows the first batch of steps instead of another batch:
+// a step that listed a frontier left the batch a round short, and the new bits
+// fell to less than a quarter of the round before's (decay: that ratio, 4 and above
+// as 1, a feature of the scheduler), so the propagation is likely to end in it.  A
+// small random graph of diameter 7 has eight rounds and one listing (10,000 nodes,
+// 256 and 512 seeds: three launches a round 200 and 216 us, 229 and 248 with a batch
+// of eight steps behind the first, 196 and 220 with one step; nine steps in every first
+// batch instead cost graphs that end sooner 3-6%).
+inline bool one_more_step(int64_t listings, float decay) { return listings > 0 && decay < 0.0625f; }
+
 }  // namespace pp
