@@ -107,13 +107,19 @@ typedef struct {
     int32_t seed_counts;        /* 1: also record per-seed counts c_i[r] */
     int32_t max_rounds;         /* capacity of the per-round logs (0: n + 1, at most 1<<20) */
     int32_t rounds_per_sync;    /* rounds launched between host convergence checks (0: adaptive:
-                                   8, then the rounds run so far, at most 64) */
+                                   8, then as many as were launched so far, at most 64, or one
+                                   where the propagation seems about to end).  A run of push
+                                   rounds with few arcs may come before them, in one launch:
+                                   only the round log bounds their number */
     int32_t use_graph;          /* 1: replay the round batch as a captured hipGraph */
     int32_t push_div;           /* heuristic: push while frontier arcs * push_div < arcs (0: 8);
                                    on a large graph a pull instead while many nodes changed in
                                    the pull before and it can stop lists early */
     uint64_t fuzz_seed;         /* PP_SCHED_FUZZ stream */
-    int32_t time_kernels;       /* 1: HIP events around every pull launch (pp_get_kernel_times) */
+    int32_t time_kernels;       /* 1: HIP events around every pull launch (pp_get_kernel_times).
+                                   Every round is then three launches, which a run without it
+                                   may take in two, or several rounds in one: the figures are
+                                   the pull's, not a propagation's */
     int32_t persistent;         /* 1: all rounds in one cooperative launch (grid barriers
                                    between phases) instead of launches per round */
     int32_t pull_k;             /* arcs per lane of the pull, 2 or 4 (0: 4); sets the pull
@@ -438,7 +444,10 @@ int pp_get_round_features(pp_run r, float *feat, int32_t cap);
  * when the run was created with sparse_pull = 1)
  * instead of the scheduler's, and stores its duration in milliseconds in
  * *ms (HIP events around the whole round, every launch of the round
- * included).  features (host [8] or NULL) receives the round's features.
+ * included).  The round is timed as three launches; a propagation of a small
+ * graph runs it in two (a push after a pull in four), or several small pushes in
+ * one launch, so the model's costs leave out what those save.  features (host [8]
+ * or NULL) receives the round's features.
  * With pp_run_snapshot / pp_run_restore a caller times a round both ways,
  * and after either kind of previous round.  PP_ESTATE if the run has
  * converged or is persistent; PP_ENOTCONV if its round log is full. */

@@ -51,7 +51,10 @@ constexpr int PUSH_CHUNK_MIN = 32;   // smallest chunk (W = 8)
 // chunks of long predecessor lists from which a push over direct slots also
 // reads their words first: so many arcs are bound by the atomics' lines, not by
 // latency (R-MAT 24, two groups of 256 seeds, the push of round 2 over 15
-// million arcs: 2.47 -> 1.52 ms; as one group of eight words 1.89 -> 1.86)
+// million arcs: 2.47 -> 1.52 ms; as one group of eight words 1.89 -> 1.86).  Whole
+// propagations, without and with: R-MAT 22 and 24, 256 seeds, 1.65 -> 1.51 and 6.16 ->
+// 5.59 ms; every round a push, R-MAT 20, 256 seeds, 1.84 -> 1.75; R-MAT 18 to 24 with 64
+// and 512 seeds and a random graph of 20M arcs the same within 2%
 constexpr int PUSH_READ_CHUNKS = 16384;
 // sparse pull: a candidate with at most this many successors gathers them
 // itself; a longer list takes the new bits by atomic OR instead

@@ -4,7 +4,10 @@
 // three launches that hand work to each other through the device control
 // block, so no host decision is needed between rounds and a batch of rounds
 // can be replayed as a captured graph.  Kernels of the direction not chosen
-// for the round return at once.
+// for the round return at once.  Small graphs and those with short lists only
+// take two launches (k_step for the first two; a push that follows a pull lists
+// its frontier in a step of its own), pushes of few arcs run one after the other
+// in one launch (k_light), and k_batch runs all rounds in one.
 //
 // Dense pull (the ball recurrence of Section 4, Sig_r(u) = Sig_{r-1}(u) OR
 // the rows of u's successors):

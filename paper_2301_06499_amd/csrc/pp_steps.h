@@ -9,7 +9,11 @@ namespace pp {
 // Late pulls stop lists early on graphs with this many arcs or more: below, a
 // round is bound by its launches and the steps' dependent loads add to it
 // (undirected R-MAT 13, 512 seeds: 3.9 -> 4.5 ms for its 16 groups; ER 10k: 192 ->
-// 204 us; but undirected R-MAT 17, 4M arcs: round 4 96 -> 45 us).
+// 204 us; but undirected R-MAT 17, 4M arcs: round 4 96 -> 45 us).  Propagations of
+// R-MATs with 16 arcs a node, 64 / 256 / 512 seeds, as steps and with early exits, us:
+// 362k arcs 174 / 198 / 222 and 197 / 227 / 282, 923k 194 / 234 / 356 and 208 / 238 / 321,
+// 1.5M 211 / 310 / 386 and 222 / 300 / 347, 3.1M 294 / 345 / 483 and 277 / 335 / 387, 6.3M 393 /
+// 468 / 716 and 352 / 410 / 532; random graphs cross between 1.5M and 3M as well.
 constexpr int64_t EXIT_MIN_ARCS = (int64_t)1 << 20;
 
 // graphs of fewer arcs run their rounds as steps of two launches, as do those
