@@ -126,7 +126,8 @@ def measured_traffic(profile: str, kernel: str):
     if rec.get("kernel") != kernel:
         return None
     csrc = os.path.join(ROOT, "paper_2301_06499_amd", "csrc")
-    src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("pp_kernels.hip", "pp_internal.h"))
+    src = b"".join(open(os.path.join(csrc, f), "rb").read()
+                   for f in ("pp_kernels.hip", "pp_internal.h", "pp_close.h", "pp_light.h", "pp_wait.h"))
     if hashlib.sha256(src).hexdigest() != rec.get("source_sha256"):
         return None
     return int(rec["fetch_bytes_per_launch"]) + int(rec["write_bytes_per_launch"])
